@@ -1,6 +1,7 @@
-// Tiled bf16 MFMA GEMM kernel template (gfx950); instantiated by k_gemm.hip.
+// Tiled MFMA GEMM kernel template (gfx950), bf16 or float32 operands;
+// instantiated by k_gemm.hip.
 //
-//   C[M][N] = A[M][K] . W[N][K]^T      (both operands K-contiguous, bf16)
+//   C[M][N] = A[M][K] . W[N][K]^T      (both operands K-contiguous)
 //
 // v_mfma_f32_16x16x32_bf16 takes the weight tile as its first operand and the
 // activation tile as its second, so accumulator element r of a lane is
@@ -8,8 +9,14 @@
 // columns of one row and the epilogue stores 8 (bf16) or 16 (fp32) contiguous
 // bytes.  A block of WGM x WGN waves owns a BM x BN tile.
 //
-// K advances BK (32, 64 or 128) at a time through ST LDS stages.  Each stage
-// holds BM activation rows and BN weight rows of 2*BK bytes, filled straight
+// float32 operands use four v_mfma_f32_16x16x4_f32 where bf16 uses one MFMA:
+// a lane's 16-byte chunk is then 4 values of K instead of 8, and MFMA r
+// contracts value r of the four lanes' chunks (the order of K within a step
+// does not matter as long as both operands share it), so the stages, the
+// swizzle and the operand reads are the same bytes in both types.
+//
+// K advances BK elements (64 to 256 bytes) at a time through ST LDS stages.
+// Each stage holds BM activation rows and BN weight rows, filled straight
 // from global memory by global_load_lds_dwordx4 (16 bytes per lane, one 1 KiB
 // run of LDS per instruction, no register staging): ST-1 stages are in flight
 // while one is multiplied.  Inside a row the 16-byte chunks are XOR-swizzled
@@ -32,7 +39,7 @@
 namespace wam {
 namespace gemm {
 
-constexpr int kBK = 32;    // K per MFMA step (and the smallest stage depth)
+constexpr int kBK = 32;    // K per bf16 MFMA step (and its smallest stage depth)
 constexpr int kGroupM = 8;
 constexpr int kXcd = 8;
 
@@ -44,12 +51,33 @@ typedef __attribute__((address_space(1))) void global_void;
 // scalar-memory operation outstanding
 constexpr int waitcnt_vm_lgkm0(int n) { return (n & 0xf) | ((n >> 4) << 14) | (0x7 << 4); }
 
-// XOR swizzle of the 16-byte chunks of an LDS row of 2*BK bytes
-template <int BK>
+// XOR swizzle of the 16-byte chunks of an LDS row of CPR chunks
+template <int CPR>
 __device__ __forceinline__ int chunk_swizzle(int row) {
-  if constexpr (BK == 32) return (row >> 1) & 3;
+  if constexpr (CPR == 4) return (row >> 1) & 3;
   else return row & 7;
 }
+
+// Operand chunk (16 bytes) of one lane and the MFMA step that consumes a
+// weight and an activation chunk.
+template <typename E>
+struct Operand;
+template <>
+struct Operand<bf16> {
+  typedef bf16x8 frag;
+  static constexpr int kSteps = 1;  // MFMAs per chunk pair
+  static __device__ __forceinline__ f32x4 mma(frag w, frag a, f32x4 c, int) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, a, c, 0, 0, 0);
+  }
+};
+template <>
+struct Operand<float> {
+  typedef f32x4 frag;
+  static constexpr int kSteps = 4;
+  static __device__ __forceinline__ f32x4 mma(frag w, frag a, f32x4 c, int r) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(w[r], a[r], c, 0, 0, 0);
+  }
+};
 
 // compiler-only memory barrier: keeps LDS and global accesses on their side
 __device__ __forceinline__ void compiler_fence() { asm volatile("" ::: "memory"); }
@@ -68,35 +96,35 @@ __device__ __forceinline__ void tile_coords(int bid, int nblocks, int tiles_m, i
   tn = in / gsz;
 }
 
-__device__ __forceinline__ void store_bf16x4(bf16* p, float a, float b, float c, float d) {
-  bf16x4 v = {static_cast<bf16>(a), static_cast<bf16>(b), static_cast<bf16>(c), static_cast<bf16>(d)};
+__device__ __forceinline__ void store4(bf16* p, f32x4 x) {
+  bf16x4 v = {static_cast<bf16>(x[0]), static_cast<bf16>(x[1]), static_cast<bf16>(x[2]), static_cast<bf16>(x[3])};
   *reinterpret_cast<bf16x4*>(p) = v;
+}
+__device__ __forceinline__ void store4(float* p, f32x4 x) { *reinterpret_cast<f32x4*>(p) = x; }
+
+__device__ __forceinline__ f32x4 gelu4(f32x4 v) {
+  return f32x4{gelu_tanh_f(v[0]), gelu_tanh_f(v[1]), gelu_tanh_f(v[2]), gelu_tanh_f(v[3])};
 }
 
 // Elementwise epilogue on four consecutive columns n..n+3 of row m.
-template <int EPI>
-__device__ __forceinline__ void epi4(const GemmArgs& a, int m, int n, float v0, float v1, float v2, float v3) {
-  const float4 b = *reinterpret_cast<const float4*>(a.bias + n);
-  v0 += b.x; v1 += b.y; v2 += b.z; v3 += b.w;
+template <typename E, int EPI>
+__device__ __forceinline__ void epi4(const GemmArgs& a, int m, int n, f32x4 v) {
+  v += *reinterpret_cast<const f32x4*>(a.bias + n);
   if constexpr (EPI == EPI_GATED_RES) {
-    const float4 g = *reinterpret_cast<const float4*>(a.gate + n);
-    float4* h = reinterpret_cast<float4*>(static_cast<float*>(a.out) + (size_t)m * a.N + n);
-    float4 hv = *h;
-    hv.x += g.x * v0; hv.y += g.y * v1; hv.z += g.z * v2; hv.w += g.w * v3;
+    f32x4* h = reinterpret_cast<f32x4*>(static_cast<float*>(a.out) + (size_t)m * a.N + n);
+    const f32x4 hv = *h + *reinterpret_cast<const f32x4*>(a.gate + n) * v;
     *h = hv;
-    if (a.copy) *reinterpret_cast<float4*>(a.copy + (size_t)m * a.N + n) = hv;
-  } else if constexpr (EPI == EPI_BIAS_GELU) {
-    store_bf16x4(static_cast<bf16*>(a.out) + (size_t)m * a.N + n, gelu_tanh_f(v0), gelu_tanh_f(v1),
-                 gelu_tanh_f(v2), gelu_tanh_f(v3));
+    if (a.copy) *reinterpret_cast<f32x4*>(a.copy + (size_t)m * a.N + n) = hv;
   } else {
-    store_bf16x4(static_cast<bf16*>(a.out) + (size_t)m * a.N + n, v0, v1, v2, v3);
+    if constexpr (EPI == EPI_BIAS_GELU) v = gelu4(v);
+    store4(static_cast<E*>(a.out) + (size_t)m * a.N + n, v);
   }
 }
 
 // Epilogue of one wave's accumulators: acc[j][i] element r is the product at
 // row mb + i*16 + lane%16, column nb + j*16 + 4*(lane/16) + r.  SPLIT stores
 // the fp32 partial of K split `split`; the others apply the role's epilogue.
-template <int EPI, int TN, int TM, bool SPLIT>
+template <typename E, int EPI, int DH, int TN, int TM, bool SPLIT>
 __device__ __forceinline__ void store_tile(const GemmArgs& a, const f32x4 (&acc)[TN][TM], int mb, int nb, int lane,
                                            int split) {
   const int lr = lane % 16, lg = lane / 16;
@@ -114,35 +142,36 @@ __device__ __forceinline__ void store_tile(const GemmArgs& a, const f32x4 (&acc)
       }
     }
   } else if constexpr (EPI == EPI_QKV) {
+    constexpr int JH = DH / 16;  // column tiles per head
     const QkvOut& qo = a.qkv;
     const int D = qo.D;
     // per-lane constants hoisted out of the store loop: bias of the lane's
     // columns and the q / k gains of its head dims (d = jj*16 + 4*lg + r)
-    f32x4 bias[TN], qg[4], kg[4];
+    f32x4 bias[TN], qg[JH], kg[JH];
 #pragma unroll
     for (int j = 0; j < TN; ++j) bias[j] = *reinterpret_cast<const f32x4*>(a.bias + nb + j * 16 + lg * 4);
 #pragma unroll
-    for (int jj = 0; jj < 4; ++jj) {
+    for (int jj = 0; jj < JH; ++jj) {
       qg[jj] = kg[jj] = f32x4{1.f, 1.f, 1.f, 1.f};
       if (qo.qk_norm) {
         qg[jj] = *reinterpret_cast<const f32x4*>(qo.q_g + jj * 16 + lg * 4);
         kg[jj] = *reinterpret_cast<const f32x4*>(qo.k_g + jj * 16 + lg * 4);
       }
-      qg[jj] *= kQLog2Scale;  // attention scores come out in log2 units
+      qg[jj] *= q_log2_scale(DH);  // attention scores come out in log2 units
     }
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
       const int m = mb + i * 16 + lr;
       const int b = m / qo.T, t = m % qo.T;
 #pragma unroll
-      for (int hs = 0; hs < TN / 4; ++hs) {
-        const int nh = nb + hs * 64;  // first column of this head
-        const int sec = nh / D, head = (nh % D) / 64;
-        f32x4 v[4];
+      for (int hs = 0; hs < TN / JH; ++hs) {
+        const int nh = nb + hs * DH;  // first column of this head
+        const int sec = nh / D, head = (nh % D) / DH;
+        f32x4 v[JH];
         float ss = 0.f;
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj) {
-          v[jj] = acc[hs * 4 + jj][i] + bias[hs * 4 + jj];
+        for (int jj = 0; jj < JH; ++jj) {
+          v[jj] = acc[hs * JH + jj][i] + bias[hs * JH + jj];
 #pragma unroll
           for (int r = 0; r < 4; ++r) ss += v[jj][r] * v[jj][r];
         }
@@ -150,23 +179,21 @@ __device__ __forceinline__ void store_tile(const GemmArgs& a, const f32x4 (&acc)
           ss += __shfl_xor(ss, 16, 64);
           ss += __shfl_xor(ss, 32, 64);
           const f32x4* gain = sec == 0 ? qg : kg;
-          const float rs = qo.qk_norm ? rsqrtf(ss * (1.0f / 64.0f) + qo.eps) : 1.0f;
+          const float rs = qo.qk_norm ? rsqrtf(ss * (1.0f / DH) + qo.eps) : 1.0f;
           if (m < a.M) {
-            bf16* dst = (sec == 0 ? qo.q : qo.k) + (((size_t)b * qo.H + head) * qo.Tpad + t) * 64;
+            E* dst = static_cast<E*>(sec == 0 ? qo.q : qo.k) + (((size_t)b * qo.H + head) * qo.Tpad + t) * DH;
 #pragma unroll
-            for (int jj = 0; jj < 4; ++jj) {
-              const f32x4 o = v[jj] * rs * gain[jj];
-              store_bf16x4(dst + jj * 16 + lg * 4, o[0], o[1], o[2], o[3]);
-            }
+            for (int jj = 0; jj < JH; ++jj) store4(dst + jj * 16 + lg * 4, v[jj] * rs * gain[jj]);
           }
         } else if (m < a.M) {
-          // V^T row d holds the tokens of each 64-key block in vt_key_pos order
-          bf16* dst = qo.vt + ((size_t)b * qo.H + head) * 64 * qo.Tpad + (t & ~63) + vt_key_pos(t & 63);
+          // V^T row d; bf16: the tokens of each 64-key block in vt_key_pos order
+          const int tp = sizeof(E) == 2 ? (t & ~63) + vt_key_pos(t & 63) : t;
+          E* dst = static_cast<E*>(qo.vt) + ((size_t)b * qo.H + head) * DH * qo.Tpad + tp;
 #pragma unroll
-          for (int jj = 0; jj < 4; ++jj)
+          for (int jj = 0; jj < JH; ++jj)
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-              dst[(size_t)(jj * 16 + lg * 4 + r) * qo.Tpad] = static_cast<bf16>(v[jj][r]);
+              dst[(size_t)(jj * 16 + lg * 4 + r) * qo.Tpad] = static_cast<E>(v[jj][r]);
         }
       }
     }
@@ -203,39 +230,39 @@ __device__ __forceinline__ void store_tile(const GemmArgs& a, const f32x4 (&acc)
           for (int j = 0; j < TN; ++j) crow[j * 4] = hv[j];
         }
       } else {
-        bf16* orow = static_cast<bf16*>(a.out) + (size_t)m * a.N + nb + lg * 4;
+        E* orow = static_cast<E*>(a.out) + (size_t)m * a.N + nb + lg * 4;
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
           const f32x4 v = acc[j][i] + bias[j];
-          if constexpr (EPI == EPI_BIAS_GELU)
-            store_bf16x4(orow + j * 16, gelu_tanh_f(v[0]), gelu_tanh_f(v[1]), gelu_tanh_f(v[2]), gelu_tanh_f(v[3]));
-          else
-            store_bf16x4(orow + j * 16, v[0], v[1], v[2], v[3]);
+          if constexpr (EPI == EPI_BIAS_GELU) store4(orow + j * 16, gelu4(v));
+          else store4(orow + j * 16, v);
         }
       }
     }
   }
 }
 
-template <int BM, int BN, int WGM, int WGN, int ST, int BK, int EPI, int ROLE, bool SPLIT>
-__global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_kernel(GemmArgs a) {
+template <typename E, int BM, int BN, int WGM, int WGN, int ST, int BK, int EPI, int DH, int ROLE, bool SPLIT>
+__device__ __forceinline__ void gemm_body(const GemmArgs& a) {
+  typedef typename Operand<E>::frag frag;
+  constexpr int EPC = 16 / sizeof(E);          // elements per 16-byte chunk
   constexpr int NW = WGM * WGN;
   constexpr int WM = BM / WGM, WN = BN / WGN;  // wave tile
   constexpr int TM = WM / 16, TN = WN / 16;
   constexpr int ROWS = BM + BN;                // LDS rows per stage: activations, then weights
-  constexpr int CPR = BK / 8;                  // 16-byte chunks per LDS row
+  constexpr int CPR = BK / EPC;                // 16-byte chunks per LDS row
   constexpr int RPI = 64 / CPR;                // rows per 1 KiB load instruction
   constexpr int NI = ROWS / RPI;               // load instructions per stage
   constexpr int IPW = NI / NW;                 // ... per wave
-  constexpr int KS = BK / kBK;                 // MFMA k-steps per stage
-  static_assert(BK == 32 || BK == 64 || BK == 128, "stage depth");
+  constexpr int KS = CPR / 4;                  // MFMA k-steps per stage (four chunks each)
+  static_assert(CPR == 4 || CPR == 8 || CPR == 16, "stage depth");
   static_assert(TM >= 1 && TN >= 1, "wave tile too small");
   static_assert(IPW >= 1 && IPW * NW == NI, "stage rows / wave mismatch");
-  static_assert(EPI != EPI_QKV || WN % 64 == 0, "QKV epilogue needs whole heads per wave");
+  static_assert(EPI != EPI_QKV || WN % DH == 0, "QKV epilogue needs whole heads per wave");
   static_assert(ST >= 2 && (ST - 2) * IPW < 64, "stage count");
   if (a.skip && *a.skip) return;
 
-  __shared__ __attribute__((aligned(1024))) bf16 sm[ST][ROWS * BK];
+  __shared__ __attribute__((aligned(1024))) E sm[ST][ROWS * BK];
 
   const int tiles_m = (a.M + BM - 1) / BM, tiles_n = a.N / BN;
   int tm, tn;
@@ -243,8 +270,8 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_kernel(GemmArgs a) {
   const int m0 = tm * BM, n0 = tn * BN;
   const int tid = threadIdx.x, lane = tid % 64, wid = tid / 64;
   const int wm = wid / WGN, wn = wid % WGN;
-  const bf16* A = static_cast<const bf16*>(a.A);
-  const bf16* W = static_cast<const bf16*>(a.W);
+  const E* A = static_cast<const E*>(a.A);
+  const E* W = static_cast<const E*>(a.W);
   const int K = a.K;
   int kbeg = 0, kend = K;
   if constexpr (SPLIT) {
@@ -258,11 +285,11 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_kernel(GemmArgs a) {
   // lane l writes LDS chunk l%CPR of row l/CPR, i.e. global chunk
   // (l%CPR) ^ swizzle.  Activation rows past M read row M-1 (their products
   // reach only output rows that are never stored).
-  const bf16* src[IPW];
+  const E* src[IPW];
 #pragma unroll
   for (int j = 0; j < IPW; ++j) {
     const int row = RPI * (wid + NW * j) + lane / CPR;
-    const int col = ((lane % CPR) ^ chunk_swizzle<BK>(row)) * 8;
+    const int col = ((lane % CPR) ^ chunk_swizzle<CPR>(row)) * EPC;
     src[j] = row < BM ? A + (size_t)min(m0 + row, a.M - 1) * K + kbeg + col
                       : W + (size_t)(n0 + row - BM) * K + kbeg + col;
   }
@@ -284,24 +311,25 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_kernel(GemmArgs a) {
   // lr of each 16-row tile (tile row offsets are multiples of 16, so the
   // swizzle depends on lr only)
   const int lr = lane % 16, lg = lane / 16;
-  const int sw = chunk_swizzle<BK>(lr);
+  const int sw = chunk_swizzle<CPR>(lr);
   const int arow = (wm * WM + lr) * BK;
   const int wrow = (BM + wn * WN + lr) * BK;
   auto compute = [&](auto S) __attribute__((always_inline)) {
     constexpr int s = decltype(S)::value;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-      const int ch = ((4 * ks + lg) ^ sw) * 8;
-      bf16x8 af[TM], wf[TN];
+      const int ch = ((4 * ks + lg) ^ sw) * EPC;
+      frag af[TM], wf[TN];
 #pragma unroll
-      for (int i = 0; i < TM; ++i) af[i] = *reinterpret_cast<const bf16x8*>(&sm[s][arow + ch + i * 16 * BK]);
+      for (int i = 0; i < TM; ++i) af[i] = *reinterpret_cast<const frag*>(&sm[s][arow + ch + i * 16 * BK]);
 #pragma unroll
-      for (int j = 0; j < TN; ++j) wf[j] = *reinterpret_cast<const bf16x8*>(&sm[s][wrow + ch + j * 16 * BK]);
+      for (int j = 0; j < TN; ++j) wf[j] = *reinterpret_cast<const frag*>(&sm[s][wrow + ch + j * 16 * BK]);
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
+      for (int r = 0; r < Operand<E>::kSteps; ++r)
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
-          acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[j], af[i], acc[j][i], 0, 0, 0);
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int i = 0; i < TM; ++i) acc[j][i] = Operand<E>::mma(wf[j], af[i], acc[j][i], r);
     }
   };
   // one K step on stage slot J: this wave's loads of stage kt have landed (the
@@ -334,7 +362,17 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_kernel(GemmArgs a) {
   // no load may still be writing this block's LDS when the block retires
   __builtin_amdgcn_s_waitcnt(0);
 
-  store_tile<EPI, TN, TM, SPLIT>(a, acc, m0 + wm * WM, n0 + wn * WN, lane, blockIdx.z);
+  store_tile<E, EPI, DH, TN, TM, SPLIT>(a, acc, m0 + wm * WM, n0 + wn * WN, lane, blockIdx.z);
+}
+
+template <int BM, int BN, int WGM, int WGN, int ST, int BK, int EPI, int ROLE, bool SPLIT>
+__global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_kernel(GemmArgs a) {
+  gemm_body<bf16, BM, BN, WGM, WGN, ST, BK, EPI, 64, ROLE, SPLIT>(a);
+}
+
+template <int BM, int BN, int WGM, int WGN, int ST, int BK, int EPI, int DH>
+__global__ __launch_bounds__(WGM* WGN * 64) void gemm_f32_kernel(GemmArgs a) {
+  gemm_body<float, BM, BN, WGM, WGN, ST, BK, EPI, DH, 0, false>(a);
 }
 
 // Split-K second pass: sum the partials in split order, then the epilogue.
@@ -347,7 +385,7 @@ __global__ __launch_bounds__(256) void gemm_splitk_reduce_kernel(GemmArgs a, int
   const int m = (int)((i4 * 4) / a.N), n = (int)((i4 * 4) % a.N);
   f32x4 sum = reinterpret_cast<const f32x4*>(a.partial)[i4];
   for (int z = 1; z < splits; ++z) sum += reinterpret_cast<const f32x4*>(a.partial + (size_t)z * a.M * a.N)[i4];
-  epi4<EPI>(a, m, n, sum[0], sum[1], sum[2], sum[3]);
+  epi4<bf16, EPI>(a, m, n, sum);
 }
 
 template <int BM, int BN, int WGM, int WGN, int ST, int BK, int ROLE>
@@ -380,6 +418,31 @@ hipError_t launch_tile(const GemmArgs& a, int splits, hipStream_t s) {
     case EPI_QKV:
       if constexpr ((BN / WGN) % 64 == 0) {
         launch_k(gemm_bf16_kernel<BM, BN, WGM, WGN, ST, BK, EPI_QKV, ROLE, false>, blocks, NT, 0, s, a);
+      } else {
+        return hipErrorInvalidValue;
+      }
+      break;
+    default:
+      return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+template <int BM, int BN, int WGM, int WGN, int ST, int BK>
+hipError_t launch_tile_f32(const GemmArgs& a, hipStream_t s) {
+  const int blocks = ((a.M + BM - 1) / BM) * (a.N / BN);
+  constexpr int NT = WGM * WGN * 64;
+  switch (a.epi) {
+    case EPI_BIAS_GELU:
+      launch_k(gemm_f32_kernel<BM, BN, WGM, WGN, ST, BK, EPI_BIAS_GELU, 64>, blocks, NT, 0, s, a);
+      break;
+    case EPI_GATED_RES:
+      launch_k(gemm_f32_kernel<BM, BN, WGM, WGN, ST, BK, EPI_GATED_RES, 64>, blocks, NT, 0, s, a);
+      break;
+    case EPI_QKV:
+      if constexpr ((BN / WGN) % 64 == 0) {
+        if (a.qkv.dh == 32) launch_k(gemm_f32_kernel<BM, BN, WGM, WGN, ST, BK, EPI_QKV, 32>, blocks, NT, 0, s, a);
+        else launch_k(gemm_f32_kernel<BM, BN, WGM, WGN, ST, BK, EPI_QKV, 64>, blocks, NT, 0, s, a);
       } else {
         return hipErrorInvalidValue;
       }

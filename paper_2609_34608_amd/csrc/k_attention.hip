@@ -1,9 +1,8 @@
 // Bidirectional softmax attention over the joint token sequence (gfx950).
 //
-// qkv_relayout: [B*T][3D] projection output -> per-head q, k ([B*H][Tpad][dh],
-// RMS-normalised with gains when QK-norm is on) and v transposed
-// ([B*H][dh][Tpad]).  Pad rows/columns beyond T are never written; the host
-// zero-fills them once.
+// q, k ([B*H][Tpad][dh]) and v^T ([B*H][dh][Tpad]) come from the QKV
+// projection's epilogue; pad rows / columns beyond T are never written, the
+// host zero-fills them once.
 //
 // bf16 flash attention (dh = 64): each wave owns 16*QT queries and keeps their
 // Q fragments in registers.  Scores are formed transposed, S^T = K Q^T, with
@@ -30,50 +29,6 @@
 namespace wam {
 
 namespace {
-
-// ------------------------------------------------------------- relayout
-template <typename T, int DH>
-__global__ __launch_bounds__(256) void qkv_relayout_kernel(RelayoutArgs a) {
-  if (a.skip && *a.skip) return;
-  constexpr int TT = 64;  // tokens per block
-  __shared__ float vs[DH][TT + 1];
-  const int t0 = blockIdx.x * TT, h = blockIdx.y, b = blockIdx.z;
-  const int tid = threadIdx.x, lane = tid % kWave, wid = tid / kWave;
-  const T* qkv = static_cast<const T*>(a.qkv);
-  const size_t bh = (size_t)b * a.H + h;
-  T* qo = static_cast<T*>(a.q) + bh * a.Tpad * DH;
-  T* ko = static_cast<T*>(a.k) + bh * a.Tpad * DH;
-  T* vo = static_cast<T*>(a.vt) + bh * DH * a.Tpad;
-  // q and k: one wave per token row, lane = feature (DH <= 64)
-  for (int tt = wid; tt < TT; tt += 4) {
-    const int t = t0 + tt;
-    if (t >= a.T) break;
-    const T* src = qkv + ((size_t)b * a.T + t) * 3 * a.D + h * DH;
-    float qv = lane < DH ? to_f32(src[lane]) : 0.f;
-    float kv = lane < DH ? to_f32(src[a.D + lane]) : 0.f;
-    const float vv = lane < DH ? to_f32(src[2 * a.D + lane]) : 0.f;
-    if (a.qk_norm) {
-      const float rq = rsqrtf(wave_sum(qv * qv) / (float)DH + a.eps);
-      const float rk = rsqrtf(wave_sum(kv * kv) / (float)DH + a.eps);
-      if (lane < DH) {
-        qv = qv * rq * a.q_g[lane];
-        kv = kv * rk * a.k_g[lane];
-      }
-    }
-    if (lane < DH) {
-      qo[(size_t)t * DH + lane] = from_f32<T>(qv);
-      ko[(size_t)t * DH + lane] = from_f32<T>(kv);
-      vs[lane][tt] = vv;
-    }
-  }
-  __syncthreads();
-  // v^T: row d holds tokens t0 .. t0+63 contiguously
-  for (int i = tid; i < DH * TT; i += 256) {
-    const int d = i / TT, tt = i % TT;
-    const int t = t0 + tt;
-    if (t < a.T) vo[(size_t)d * a.Tpad + t] = from_f32<T>(vs[d][tt]);
-  }
-}
 
 // ------------------------------------------------------------- bf16 flash attention
 constexpr int kDh = 64;
@@ -784,58 +739,185 @@ __global__ __launch_bounds__(512) void attn_bf16_pingpong_kernel(AttnArgs a) {
 }
 
 // ------------------------------------------------------------- fp32 attention
-// One thread per query, online softmax over all keys (parity mode only).
-template <int DH>
-__global__ __launch_bounds__(64) void attn_f32_kernel(AttnArgs a) {
+// Flash attention of the float32 mode on the fp32 matrix cores
+// (v_mfma_f32_16x16x4_f32: 2048 FLOP in 32 cycles, so a wave needs two
+// floats a lane per 32 cycles and the matrix pipe is the bound, not the
+// loads).  Same transposed scheme as the bf16 kernels: S^T = K Q^T leaves a
+// lane with the scores of one query (keys 4g + r of each 16-key tile), and
+// O^T += V^T P^T takes P straight from those registers: MFMA r of a 16-key
+// tile contracts the keys {4g + r}, so that a lane's V^T operands of the four
+// MFMAs are one 16-byte load, and likewise its K operands with the head
+// dimensions taken in the order 16c + 4g + r on both sides.  Operands come
+// from global memory (L1 / L2) into registers, without LDS or barriers: V^T of
+// a 64-key tile is requested before its QK^T MFMAs and the next K tile before
+// the PV MFMAs, 2048 cycles each at head size 64.  q arrives scaled by
+// log2(e) / sqrt(dh) from the QKV epilogue.
+// KS > 1 (short sequences, where one 16-query tile per wave leaves SIMDs
+// idle): the four waves of a block split the key tiles of the same queries
+// and combine their (m, l, O) through LDS, in wave order.
+// T = 864, 12 heads of 64: 1387 us with one thread per query on the vector
+// pipe, 46 us here (19 us at the fp32 matrix rate).
+template <int DH, int QT, int KS>
+__global__ __launch_bounds__(256, 2) void attn_f32_kernel(AttnArgs a) {
   if (a.skip && *a.skip) return;
+  static_assert(KS == 1 || KS == 4, "key split");
+  constexpr int DT = DH / 16;
   const int bh = blockIdx.y;
   const int b = bh / a.H, h = bh % a.H;
-  const int q = blockIdx.x * 64 + threadIdx.x;
-  if (q >= a.T) return;
-  const float* Q = static_cast<const float*>(a.q) + ((size_t)bh * a.Tpad + q) * DH;
-  const float* Kg = static_cast<const float*>(a.k) + (size_t)bh * a.Tpad * DH;
-  const float* Vt = static_cast<const float*>(a.vt) + (size_t)bh * DH * a.Tpad;
-  float qv[DH], acc[DH];
-  const float sc = rsqrtf((float)DH);
+  const int lane = threadIdx.x % 64, wid = threadIdx.x / 64;
+  const int g = lane / 16, lr = lane % 16;
+  const int q0 = (KS == 1 ? blockIdx.x * 4 + wid : blockIdx.x) * QT * 16;
+  if (KS == 1 && q0 >= a.T) return;
+  const float* Q = static_cast<const float*>(a.q) + ((size_t)bh * a.Tpad + q0 + lr) * DH + 4 * g;
+  const float* Kg = static_cast<const float*>(a.k) + ((size_t)bh * a.Tpad + lr) * DH + 4 * g;
+  const float* Vt = static_cast<const float*>(a.vt) + ((size_t)bh * DH + lr) * a.Tpad + 4 * g;
+
+  f32x4 qf[QT][DT], o[DT][QT];
+  float m[QT], l[QT];
 #pragma unroll
-  for (int d = 0; d < DH; ++d) {
-    qv[d] = Q[d] * sc;
-    acc[d] = 0.f;
+  for (int qt = 0; qt < QT; ++qt) {
+#pragma unroll
+    for (int c = 0; c < DT; ++c) {
+      // q0 + 16 qt + lr < Tpad: Tpad is a multiple of 64 and q0 < T of 16 QT <= 64
+      qf[qt][c] = *reinterpret_cast<const f32x4*>(Q + (size_t)qt * 16 * DH + c * 16);
+      o[c][qt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    m[qt] = -INFINITY;
+    l[qt] = 0.f;
   }
-  float m = -INFINITY, l = 0.f;
-  for (int j = 0; j < a.T; ++j) {
-    float s = 0.f;
+  const int nkb = a.Tpad / kKB;
+  f32x4 kf[4][DT], vf[4][DT];
+  auto load_k = [&](int kb) __attribute__((always_inline)) {
 #pragma unroll
-    for (int d = 0; d < DH; ++d) s += qv[d] * Kg[(size_t)j * DH + d];
-    const float mn = fmaxf(m, s);
-    const float corr = __expf(m - mn);
-    const float p = __expf(s - mn);
-    l = l * corr + p;
+    for (int kt = 0; kt < 4; ++kt)
 #pragma unroll
-    for (int d = 0; d < DH; ++d) acc[d] = acc[d] * corr + p * Vt[(size_t)d * a.Tpad + j];
-    m = mn;
+      for (int c = 0; c < DT; ++c)
+        kf[kt][c] = *reinterpret_cast<const f32x4*>(Kg + (size_t)(kb * kKB + kt * 16) * DH + c * 16);
+  };
+  int kb = KS == 1 ? 0 : wid;
+  if (kb < nkb) load_k(kb);
+  for (; kb < nkb; kb += KS) {
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+      for (int d = 0; d < DT; ++d)
+        vf[kt][d] = *reinterpret_cast<const f32x4*>(Vt + (size_t)d * 16 * a.Tpad + kb * kKB + kt * 16);
+    __builtin_amdgcn_sched_barrier(0);  // requested before the MFMAs, not sunk to their use
+    f32x4 s[4][QT];
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+      for (int qt = 0; qt < QT; ++qt) s[kt][qt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // accumulators of different key and query tiles in turn, so that no MFMA
+    // waits for the one before it
+#pragma unroll
+    for (int c = 0; c < DT; ++c)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+          for (int qt = 0; qt < QT; ++qt)
+            s[kt][qt] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[kt][c][r], qf[qt][c][r], s[kt][qt], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    if (kb + KS < nkb) load_k(kb + KS);
+    __builtin_amdgcn_sched_barrier(0);
+    if (kb == nkb - 1) {  // only the last key tile holds keys >= T
+#pragma unroll
+      for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const bool live = kb * kKB + kt * 16 + 4 * g + r < a.T;
+#pragma unroll
+          for (int qt = 0; qt < QT; ++qt) s[kt][qt][r] = live ? s[kt][qt][r] : -INFINITY;
+        }
+    }
+#pragma unroll
+    for (int qt = 0; qt < QT; ++qt) {
+      float mx = m[qt];
+#pragma unroll
+      for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) mx = fmaxf(mx, s[kt][qt][r]);
+      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+      const float corr = __builtin_amdgcn_exp2f(m[qt] - mx);
+      m[qt] = mx;
+      float sum = 0.f;
+#pragma unroll
+      for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          s[kt][qt][r] = __builtin_amdgcn_exp2f(s[kt][qt][r] - mx);
+          sum += s[kt][qt][r];
+        }
+      l[qt] = l[qt] * corr + sum;
+#pragma unroll
+      for (int d = 0; d < DT; ++d) o[d][qt] *= corr;
+    }
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int d = 0; d < DT; ++d)
+#pragma unroll
+          for (int qt = 0; qt < QT; ++qt)
+            o[d][qt] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[kt][d][r], s[kt][qt][r], o[d][qt], 0, 0, 0);
   }
-  float* orow = static_cast<float*>(a.out) + ((size_t)b * a.T + q) * a.D + h * DH;
-  const float inv = 1.0f / l;
+  // each lane summed its own keys of its query: add the four lane groups
 #pragma unroll
-  for (int d = 0; d < DH; ++d) orow[d] = acc[d] * inv;
+  for (int qt = 0; qt < QT; ++qt) {
+    l[qt] += __shfl_xor(l[qt], 16, 64);
+    l[qt] += __shfl_xor(l[qt], 32, 64);
+  }
+  float* out = static_cast<float*>(a.out);
+  auto store = [&](int qt, int d, f32x4 v) __attribute__((always_inline)) {
+    const int q = q0 + qt * 16 + lr;
+    if (q < a.T) *reinterpret_cast<f32x4*>(out + ((size_t)b * a.T + q) * a.D + h * DH + d * 16 + 4 * g) = v;
+  };
+  if constexpr (KS == 1) {
+#pragma unroll
+    for (int qt = 0; qt < QT; ++qt) {
+      const float inv = 1.0f / l[qt];
+#pragma unroll
+      for (int d = 0; d < DT; ++d) store(qt, d, o[d][qt] * inv);
+    }
+  } else {
+    __shared__ f32x4 xo[KS][QT][DT][64];
+    __shared__ float xm[KS][QT][16], xl[KS][QT][16];
+#pragma unroll
+    for (int qt = 0; qt < QT; ++qt) {
+#pragma unroll
+      for (int d = 0; d < DT; ++d) xo[wid][qt][d][lane] = o[d][qt];
+      if (g == 0) {
+        xm[wid][qt][lr] = m[qt];
+        xl[wid][qt][lr] = l[qt];
+      }
+    }
+    __syncthreads();
+    // wave w finishes head-dimension tile w; a wave that had no key tile
+    // (m = -inf, O = l = 0) adds nothing
+    if (wid >= DT) return;
+#pragma unroll
+    for (int qt = 0; qt < QT; ++qt) {
+      float mx = xm[0][qt][lr];
+#pragma unroll
+      for (int w = 1; w < KS; ++w) mx = fmaxf(mx, xm[w][qt][lr]);
+      float lt = 0.f;
+      f32x4 ot = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int w = 0; w < KS; ++w) {
+        const float f = __builtin_amdgcn_exp2f(xm[w][qt][lr] - mx);
+        lt += f * xl[w][qt][lr];
+        ot += f * xo[w][qt][wid][lane];
+      }
+      store(qt, wid, ot * (1.0f / lt));
+    }
+  }
 }
 
 }  // namespace
-
-hipError_t launch_qkv_relayout(const RelayoutArgs& a, bool bf16_mode, hipStream_t s) {
-  dim3 grid((a.T + 63) / 64, a.H, a.B);
-  if (a.dh == 64) {
-    if (bf16_mode) launch_k(qkv_relayout_kernel<bf16, 64>, grid, 256, 0, s, a);
-    else launch_k(qkv_relayout_kernel<float, 64>, grid, 256, 0, s, a);
-  } else if (a.dh == 32) {
-    if (bf16_mode) launch_k(qkv_relayout_kernel<bf16, 32>, grid, 256, 0, s, a);
-    else launch_k(qkv_relayout_kernel<float, 32>, grid, 256, 0, s, a);
-  } else {
-    return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
 
 // grid for qt query tiles per wave and nw waves per block
 // (qt, nw, st): query tiles of 16 per wave, waves per block, LDS stages of
@@ -906,6 +988,16 @@ float attention_score_bound(const float* q_g, const float* k_g) {
   return kQLog2Scale * 64.0f * gq * gk * (1.0f + 1.0f / 128.0f) + 1e-3f;
 }
 
+template <int DH>
+hipError_t launch_attention_f32(const AttnArgs& a, hipStream_t s) {
+  const int tiles = (a.T + 15) / 16, heads = a.B * a.H;
+  const long units = (long)tiles * heads;
+  if (units >= 8192) launch_k(attn_f32_kernel<DH, 2, 1>, dim3((tiles + 7) / 8, heads), 256, 0, s, a);
+  else if (units >= 2048) launch_k(attn_f32_kernel<DH, 1, 1>, dim3((tiles + 3) / 4, heads), 256, 0, s, a);
+  else launch_k(attn_f32_kernel<DH, 1, 4>, dim3(tiles, heads), 256, 0, s, a);
+  return hipGetLastError();
+}
+
 hipError_t launch_attention(const AttnArgs& a, bool bf16_mode, hipStream_t s) {
   if (bf16_mode && a.bounded && a.variant != WAM_ATTN_RUNNING_MAX) {
     if (a.variant == WAM_ATTN_PINGPONG) return launch_attention_cfg(a, 4, 8, 4, s, ATTN_PINGPONG);
@@ -930,11 +1022,13 @@ hipError_t launch_attention(const AttnArgs& a, bool bf16_mode, hipStream_t s) {
     if (blocks >= 256) return launch_attention_cfg(a, 2, 4, 2, s, ATTN_RUNNING);
     return launch_attention_cfg(a, 1, 4, 4, s, ATTN_RUNNING);
   }
-  dim3 grid((a.T + 63) / 64, a.B * a.H);
-  if (a.dh == 64) launch_k(attn_f32_kernel<64>, grid, 64, 0, s, a);
-  else if (a.dh == 32) launch_k(attn_f32_kernel<32>, grid, 64, 0, s, a);
-  else return hipErrorInvalidValue;
-  return hipGetLastError();
+  // fp32: enough 16-query tiles for two waves per SIMD without a key split
+  // (2048 waves), else four waves split the keys of one tile; two tiles per
+  // wave (half the K / V^T traffic) once that still leaves four waves per SIMD
+  if (a.T <= 0 || a.Tpad % kKB || a.T > a.Tpad || a.T <= a.Tpad - kKB) return hipErrorInvalidValue;
+  if (a.dh == 64) return launch_attention_f32<64>(a, s);
+  if (a.dh == 32) return launch_attention_f32<32>(a, s);
+  return hipErrorInvalidValue;
 }
 
 }  // namespace wam

@@ -1,6 +1,6 @@
 // Projection GEMMs of the DiT block: tile-configuration table, planner and
-// dispatch for the bf16 MFMA kernel of gemm_tile.h, plus a plain LDS-tiled
-// fp32 kernel for the float32 parity mode.
+// dispatch for the MFMA kernels of gemm_tile.h (bf16, and float32 for the
+// float32 mode).
 #include "gemm_tile.h"
 
 namespace wam {
@@ -8,6 +8,7 @@ namespace wam {
 namespace {
 
 using gemm::launch_tile;
+using gemm::launch_tile_f32;
 
 // ---------------------------------------------------------------- configs
 struct TileCfg {
@@ -89,68 +90,27 @@ hipError_t launch_role(const GemmArgs& a, int cfg, int splits, hipStream_t s) {
 bool qkv_ok(int c) { return (kCfgs[c].bn / kCfgs[c].wgn) % 64 == 0; }
 
 // ---------------------------------------------------------------- fp32
-constexpr int kFT = 64, kFK = 16;
-
-template <int EPI>
-__device__ __forceinline__ void epi1_f32(const GemmArgs& a, int m, int n, float acc) {
-  if (m >= a.M) return;
-  const float v = acc + a.bias[n];
-  if constexpr (EPI == EPI_GATED_RES) {
-    float* h = static_cast<float*>(a.out) + (size_t)m * a.N + n;
-    const float nv = *h + a.gate[n] * v;
-    *h = nv;
-    if (a.copy) a.copy[(size_t)m * a.N + n] = nv;
-  } else if constexpr (EPI == EPI_BIAS_GELU) {
-    static_cast<float*>(a.out)[(size_t)m * a.N + n] = gelu_tanh_f(v);
-  } else {
-    static_cast<float*>(a.out)[(size_t)m * a.N + n] = v;
-  }
-}
-
-template <int EPI>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs a) {
-  if (a.skip && *a.skip) return;
-  __shared__ float As[kFK][kFT + 4];
-  __shared__ float Bs[kFK][kFT + 4];
-  const int m0 = blockIdx.y * kFT, n0 = blockIdx.x * kFT;
-  const int tid = threadIdx.x, ty = tid / 16, tx = tid % 16;
-  const float* A = static_cast<const float*>(a.A);
-  const float* W = static_cast<const float*>(a.W);
-  float acc[4][4] = {};
-  const int lrow = tid / 4, lk = (tid % 4) * 4;
-  for (int k0 = 0; k0 < a.K; k0 += kFK) {
-    {
-      const int m = m0 + lrow;
-      float4 v = m < a.M ? *reinterpret_cast<const float4*>(A + (size_t)m * a.K + k0 + lk)
-                         : make_float4(0.f, 0.f, 0.f, 0.f);
-      As[lk + 0][lrow] = v.x; As[lk + 1][lrow] = v.y; As[lk + 2][lrow] = v.z; As[lk + 3][lrow] = v.w;
-      const int n = n0 + lrow;
-      float4 w = n < a.N ? *reinterpret_cast<const float4*>(W + (size_t)n * a.K + k0 + lk)
-                         : make_float4(0.f, 0.f, 0.f, 0.f);
-      Bs[lk + 0][lrow] = w.x; Bs[lk + 1][lrow] = w.y; Bs[lk + 2][lrow] = w.z; Bs[lk + 3][lrow] = w.w;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < kFK; ++k) {
-      float av[4], bv[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) av[i] = As[k][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) bv[j] = Bs[k][tx * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] += av[i] * bv[j];
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = n0 + tx * 4 + j;
-      if (n < a.N) epi1_f32<EPI>(a, m0 + ty * 4 + i, n, acc[i][j]);
-    }
+// The fp32 matrix rate (157 TFLOP/s, a sixteenth of bf16) leaves loads and
+// LDS far from their limits at any tile, so the tile only has to spread the
+// work evenly: 64x64 where the last wave of blocks costs less than the better
+// balance of 32-row or 32x32 tiles (counted as the tile area of the busiest
+// CU; the small tiles pay ~10% for their shorter MFMA runs).  One wave column
+// of 64 where a wave has to own whole heads (QKV epilogue).
+// Small model, M = 864, against 64x64 tiles on the vector pipe (15-20
+// TFLOP/s): QKV 65 -> 36 us, attention output 58 -> 16, MLP-up 79 -> 52,
+// MLP-down 214 -> 52.
+hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t s) {
+  if (a.K % 32 || a.N % 64) return hipErrorInvalidValue;
+  auto cost = [&](int bm, int bn, double per) {
+    const long blocks = (long)((a.M + bm - 1) / bm) * (a.N / bn);
+    return (double)((blocks + 255) / 256) * bm * bn * per;
+  };
+  const double c64 = cost(64, 64, 1.0);
+  if (a.epi == EPI_QKV)
+    return cost(32, 64, 1.05) < c64 ? launch_tile_f32<32, 64, 2, 1, 4, 32>(a, s)
+                                    : launch_tile_f32<64, 64, 4, 1, 3, 32>(a, s);
+  return cost(32, 32, 1.1) < c64 ? launch_tile_f32<32, 32, 2, 2, 4, 32>(a, s)
+                                 : launch_tile_f32<64, 64, 2, 2, 3, 32>(a, s);
 }
 
 }  // namespace
@@ -248,15 +208,7 @@ hipError_t launch_gemm(const GemmArgs& a, bool bf16_mode, hipStream_t s) {
     const GemmPlan p = plan_gemm(a.M, a.N, a.K, a.epi);
     return launch_gemm_cfg(a, p.cfg, p.splits, s);
   }
-  if (a.K % kFK || a.epi == EPI_QKV) return hipErrorInvalidValue;
-  dim3 grid((a.N + kFT - 1) / kFT, (a.M + kFT - 1) / kFT);
-  switch (a.epi) {
-    case EPI_BIAS: launch_k(gemm_f32_kernel<EPI_BIAS>, grid, 256, 0, s, a); break;
-    case EPI_BIAS_GELU: launch_k(gemm_f32_kernel<EPI_BIAS_GELU>, grid, 256, 0, s, a); break;
-    case EPI_GATED_RES: launch_k(gemm_f32_kernel<EPI_GATED_RES>, grid, 256, 0, s, a); break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
+  return launch_gemm_f32(a, s);
 }
 
 }  // namespace wam

@@ -162,7 +162,7 @@ DevLayout dev_layout(const Dims& d) {
 }
 
 struct WsLayout {
-  size_t h, hq, pa, Ra, u, qkv, q, k, vt, attn, mlp, e, a1, sc, mod, gpart, v;
+  size_t h, hq, pa, Ra, u, q, k, vt, attn, mlp, e, a1, sc, mod, gpart, v;
   size_t x_bar, x_r, x_init, x_work, rr_rows, rr_res, tr_rms, or_sums, gsplit, total;
   size_t rr_flag, hist_stats, hist_flag, cond_buf;
   size_t gpart_floats;
@@ -179,7 +179,6 @@ WsLayout ws_layout(const Dims& d) {
   const size_t MD = (size_t)d.M * d.D;
   w.h = take(MD * 4); w.hq = take(MD * 4); w.pa = take(MD * 4); w.Ra = take(MD * 4);
   w.u = take(MD * d.act);
-  w.qkv = take(MD * 3 * d.act);
   const size_t head = (size_t)d.B * d.H * d.Tpad * d.dh;
   w.q = take(head * d.act); w.k = take(head * d.act); w.vt = take(head * d.act);
   w.attn = take(MD * d.act);
@@ -391,21 +390,11 @@ int run_layer(wam_t h, int l, const int* skip = nullptr, float* copy = nullptr) 
     GemmArgs g{};
     g.A = h->S<char>(ws.u); g.W = qkv_w; g.bias = qkv_b; g.M = d.M; g.N = (int)(3 * D); g.K = (int)D;
     g.role = 0; g.partial = h->S(ws.gsplit); g.skip = skip;
-    if (d.bf) {
-      // projection with q/k RMS-norm and the head-major relayout fused in
-      g.epi = EPI_QKV;
-      g.qkv = QkvOut{h->S<bf16>(ws.q), h->S<bf16>(ws.k), h->S<bf16>(ws.vt), q_g, k_g,
-                     d.T, d.Tpad, d.H, d.D, h->cfg.qk_norm, h->cfg.ln_eps};
-      HIPCHK(h, launch_gemm(g, true, s));
-    } else {
-      g.epi = EPI_BIAS; g.out = h->S<char>(ws.qkv);
-      HIPCHK(h, launch_gemm(g, false, s));
-    }
-  }
-  if (!d.bf) {
-    RelayoutArgs r{h->S<char>(ws.qkv), q_g, k_g, h->S<char>(ws.q), h->S<char>(ws.k), h->S<char>(ws.vt),
-                   d.B, d.H, d.T, d.Tpad, d.dh, d.D, h->cfg.qk_norm, h->cfg.ln_eps, skip};
-    HIPCHK(h, launch_qkv_relayout(r, false, s));
+    // projection with q/k RMS-norm and the head-major layout fused in
+    g.epi = EPI_QKV;
+    g.qkv = QkvOut{h->S<char>(ws.q), h->S<char>(ws.k), h->S<char>(ws.vt), q_g, k_g,
+                   d.T, d.Tpad, d.H, d.D, d.dh, h->cfg.qk_norm, h->cfg.ln_eps};
+    HIPCHK(h, launch_gemm(g, d.bf, s));
   }
   {
     ProfScope ps(h, WAM_KC_ATTENTION, 4.0 * d.B * (double)d.T * d.T * D);

@@ -57,9 +57,12 @@ __device__ __forceinline__ void static_for(F&& f) {
   static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
-// The bf16 QKV epilogue stores q pre-multiplied by log2(e) / sqrt(64), so the
-// bf16 attention kernel's scores are already the exponents of exp2.
-constexpr float kQLog2Scale = 0.18033688011112042f;  // log2(e) / 8
+// The QKV epilogue stores q pre-multiplied by log2(e) / sqrt(dh), so the
+// attention kernels' scores are already the exponents of exp2.
+constexpr float kQLog2Scale = 0.18033688011112042f;  // log2(e) / sqrt(64)
+__host__ __device__ constexpr float q_log2_scale(int dh) {
+  return dh == 64 ? kQLog2Scale : 0.25503486164919736f;  // log2(e) / sqrt(32)
+}
 
 // Key order inside each 64-key block of the stored V^T rows (bf16 path): key
 // 32c + 16h + 4g + r sits at 32c + 8g + 4h + r, so that the eight keys one
@@ -109,17 +112,17 @@ enum GemmEpilogue : int {
   EPI_BIAS = 0,       // out[m,n] = acc + bias[n]                       (act type)
   EPI_BIAS_GELU = 1,  // out[m,n] = gelu(acc + bias[n])                 (act type)
   EPI_GATED_RES = 2,  // h[m,n] += gate[n] * (acc + bias[n])            (float32)
-  EPI_QKV = 3,        // q,k RMS-normalised per head -> [B*H][Tpad][64], v -> [B*H][64][Tpad]
+  EPI_QKV = 3,        // q,k RMS-normalised per head -> [B*H][Tpad][dh], v -> [B*H][dh][Tpad]
 };
 
-// Destination of the QKV epilogue (bf16 mode, head size 64).
+// Destination of the QKV epilogue (act type; head size 64, or 32 in float32 mode).
 struct QkvOut {
-  bf16* q;
-  bf16* k;
-  bf16* vt;
+  void* q;
+  void* k;
+  void* vt;
   const float* q_g;
   const float* k_g;
-  int T, Tpad, H, D, qk_norm;
+  int T, Tpad, H, D, dh, qk_norm;
   float eps;
 };
 
@@ -175,21 +178,6 @@ hipError_t launch_attention_cfg(const AttnArgs& a, int qt, int nw, int st, hipSt
 // Largest score magnitude, log2 units, that the bf16 QKV epilogue can produce
 // for head size 64 with QK-norm gains q_g, k_g (host arrays of 64)
 float attention_score_bound(const float* q_g, const float* k_g);
-
-// qkv [B*T][3D] -> q, k (optionally RMS-normalised with gains) and v^T
-struct RelayoutArgs {
-  const void* qkv;
-  const float* q_g;
-  const float* k_g;
-  void* q;
-  void* k;
-  void* vt;
-  int B, H, T, Tpad, dh, D;
-  int qk_norm;
-  float eps;
-  const int* skip;
-};
-hipError_t launch_qkv_relayout(const RelayoutArgs& a, bool bf16_mode, hipStream_t s);
 
 // ---------------------------------------------------------------- small kernels
 // y[n] = out_act(sum_k in_act(x[k]) W[k][n] + b[n]), W row-major [K][N]

@@ -1,0 +1,56 @@
+"""One DiT layer against the float64 oracle at the sizes where the projection
+and attention kernels change form: tile edges, remainders and the branches of
+their dispatch, every row of the layer's update h_1 - h_0."""
+import numpy as np
+import pytest
+
+from oracle import dit as OD
+from synth import get_workload, make_weights, make_initial_noise, make_observations
+from gpu_common import device, to_dev, f32_sigmas
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dev():
+    return device()
+
+
+def _update_error(dev, spec, k=3):
+    """max |update error| over max |update|, and the float32 spacing of h over
+    max |update| (the rounding of the stored h)."""
+    from paper_2609_34608_amd import runtime as R
+    W = make_weights(spec, bias_std=0.02, gain_std=0.1, weight_std=0.05)
+    m = R.WamModel(R.config_of(spec), W, device=dev)
+    sig = f32_sigmas(spec.K)
+    m.set_schedule(sig)
+    x, cond = to_dev(make_initial_noise(spec), dev), to_dev(make_observations(spec, 0)[0], dev)
+    h0 = m.hidden(k, x, cond, 0).cpu().numpy()
+    h1 = m.hidden(k, x, cond, 1).cpu().numpy()
+    m.close()
+    ref = OD.dit_layer(W, spec, 0, h0, OD.cond_vector(W, sig[k])) - h0
+    upd = np.max(np.abs(ref))
+    return float(np.max(np.abs((h1 - h0) - ref)) / upd), float(2.0 ** -24 * np.max(np.abs(h1)) / upd)
+
+
+def _spec(dtype, B, T, D, dh, F, qk_norm=True):
+    na, no = min(7, T // 3), min(5, T // 4)
+    return get_workload("tiny").replace(L=1, B=B, D=D, H=D // dh, F=F, Nv=T - na - no, Na=na, No=no, dtype=dtype,
+                                        qk_norm=qk_norm)
+
+
+# float32: (B, T, D, head size, F).  Lengths around the 16-query tiles and the
+# 64-key tiles (one to five key tiles over four waves, so some waves get none);
+# 2112 query tiles (no key split) and 8320 (two tiles per wave); projections in
+# 32x32 / 32x64 and 64x64 tiles; head sizes 32 and 64, QK-norm on and off.
+@pytest.mark.parametrize("B,T,D,dh,F,qk_norm", [
+    (1, 3, 64, 32, 64, True), (1, 16, 64, 64, 192, True), (2, 17, 128, 32, 320, False), (1, 63, 192, 64, 768, True),
+    (3, 64, 128, 64, 512, True), (1, 65, 320, 32, 1280, True), (1, 129, 192, 32, 448, False),
+    (2, 321, 256, 64, 1024, True), (1, 2100, 512, 32, 512, True), (16, 1030, 256, 32, 256, True),
+])
+def test_float32_layer(dev, B, T, D, dh, F, qk_norm):
+    err, ulp = _update_error(dev, _spec("fp32", B, T, D, dh, F, qk_norm))
+    print(f"fp32 B={B} T={T} D={D} dh={dh} F={F}: update rel err {err:.2e}, h rounding {ulp:.2e}")
+    # rounding of the stored h0 and h1 (two roundings each), and the first-order
+    # bound of the float32 sums (one 2^-24 per term)
+    assert err <= 4 * ulp + (F + 3 * D) * 2.0 ** -24, (err, ulp)
