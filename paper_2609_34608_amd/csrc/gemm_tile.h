@@ -29,9 +29,7 @@
 // bare s_barrier (a workgroup fence would drain every load in flight).
 // Blocks are renumbered so that each XCD (dispatch is round-robin over 8 XCDs)
 // gets a contiguous run of a grouped tile order and shares A rows / W columns
-// in its own L2.  With SPLIT, gridDim.z splits K: every split stores an fp32
-// partial tile and a second pass sums the partials in split order
-// (deterministic) and applies the epilogue.
+// in its own L2.
 #pragma once
 
 #include "wam_internal.h"
@@ -106,42 +104,12 @@ __device__ __forceinline__ f32x4 gelu4(f32x4 v) {
   return f32x4{gelu_tanh_f(v[0]), gelu_tanh_f(v[1]), gelu_tanh_f(v[2]), gelu_tanh_f(v[3])};
 }
 
-// Elementwise epilogue on four consecutive columns n..n+3 of row m.
-template <typename E, int EPI>
-__device__ __forceinline__ void epi4(const GemmArgs& a, int m, int n, f32x4 v) {
-  v += *reinterpret_cast<const f32x4*>(a.bias + n);
-  if constexpr (EPI == EPI_GATED_RES) {
-    f32x4* h = reinterpret_cast<f32x4*>(static_cast<float*>(a.out) + (size_t)m * a.N + n);
-    const f32x4 hv = *h + *reinterpret_cast<const f32x4*>(a.gate + n) * v;
-    *h = hv;
-    if (a.copy) *reinterpret_cast<f32x4*>(a.copy + (size_t)m * a.N + n) = hv;
-  } else {
-    if constexpr (EPI == EPI_BIAS_GELU) v = gelu4(v);
-    store4(static_cast<E*>(a.out) + (size_t)m * a.N + n, v);
-  }
-}
-
 // Epilogue of one wave's accumulators: acc[j][i] element r is the product at
-// row mb + i*16 + lane%16, column nb + j*16 + 4*(lane/16) + r.  SPLIT stores
-// the fp32 partial of K split `split`; the others apply the role's epilogue.
-template <typename E, int EPI, int DH, int TN, int TM, bool SPLIT>
-__device__ __forceinline__ void store_tile(const GemmArgs& a, const f32x4 (&acc)[TN][TM], int mb, int nb, int lane,
-                                           int split) {
+// row mb + i*16 + lane%16, column nb + j*16 + 4*(lane/16) + r.
+template <typename E, int EPI, int DH, int TN, int TM>
+__device__ __forceinline__ void store_tile(const GemmArgs& a, const f32x4 (&acc)[TN][TM], int mb, int nb, int lane) {
   const int lr = lane % 16, lg = lane / 16;
-  if constexpr (SPLIT) {
-    // fp32 partial tile of this K split; the role's reduce pass finishes it
-    float* P = a.partial + (size_t)split * a.M * a.N;
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      const int m = mb + i * 16 + lr;
-      if (m >= a.M) continue;
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int n = nb + j * 16 + lg * 4;
-        *reinterpret_cast<f32x4*>(P + (size_t)m * a.N + n) = acc[j][i];
-      }
-    }
-  } else if constexpr (EPI == EPI_QKV) {
+  if constexpr (EPI == EPI_QKV) {
     constexpr int JH = DH / 16;  // column tiles per head
     const QkvOut& qo = a.qkv;
     const int D = qo.D;
@@ -242,7 +210,7 @@ __device__ __forceinline__ void store_tile(const GemmArgs& a, const f32x4 (&acc)
   }
 }
 
-template <typename E, int BM, int BN, int WGM, int WGN, int ST, int BK, int EPI, int DH, int ROLE, bool SPLIT>
+template <typename E, int BM, int BN, int WGM, int WGN, int ST, int BK, int EPI, int DH>
 __device__ __forceinline__ void gemm_body(const GemmArgs& a) {
   typedef typename Operand<E>::frag frag;
   constexpr int EPC = 16 / sizeof(E);          // elements per 16-byte chunk
@@ -260,11 +228,12 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a) {
   static_assert(IPW >= 1 && IPW * NW == NI, "stage rows / wave mismatch");
   static_assert(EPI != EPI_QKV || WN % DH == 0, "QKV epilogue needs whole heads per wave");
   static_assert(ST >= 2 && (ST - 2) * IPW < 64, "stage count");
+  static_assert(64 % WN == 0, "ragged N: a wave's columns lie inside N or past it");
   if (a.skip && *a.skip) return;
 
   __shared__ __attribute__((aligned(1024))) E sm[ST][ROWS * BK];
 
-  const int tiles_m = (a.M + BM - 1) / BM, tiles_n = a.N / BN;
+  const int tiles_m = (a.M + BM - 1) / BM, tiles_n = (a.N + BN - 1) / BN;
   int tm, tn;
   tile_coords(blockIdx.x, gridDim.x, tiles_m, tiles_n, tm, tn);
   const int m0 = tm * BM, n0 = tn * BN;
@@ -273,25 +242,19 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a) {
   const E* A = static_cast<const E*>(a.A);
   const E* W = static_cast<const E*>(a.W);
   const int K = a.K;
-  int kbeg = 0, kend = K;
-  if constexpr (SPLIT) {
-    const int per = K / gridDim.z;  // host guarantees divisibility by BK * splits
-    kbeg = blockIdx.z * per;
-    kend = kbeg + per;
-  }
-  const int nk = (kend - kbeg) / BK;
+  const int nk = K / BK;
 
   // Load instruction j of this wave fills LDS rows RPI*(wid + NW*j) .. +RPI-1;
   // lane l writes LDS chunk l%CPR of row l/CPR, i.e. global chunk
-  // (l%CPR) ^ swizzle.  Activation rows past M read row M-1 (their products
-  // reach only output rows that are never stored).
+  // (l%CPR) ^ swizzle.  Activation rows past M read row M-1 and weight rows
+  // past N row N-1 (their products reach only outputs that are never stored).
   const E* src[IPW];
 #pragma unroll
   for (int j = 0; j < IPW; ++j) {
     const int row = RPI * (wid + NW * j) + lane / CPR;
     const int col = ((lane % CPR) ^ chunk_swizzle<CPR>(row)) * EPC;
-    src[j] = row < BM ? A + (size_t)min(m0 + row, a.M - 1) * K + kbeg + col
-                      : W + (size_t)(n0 + row - BM) * K + kbeg + col;
+    src[j] = row < BM ? A + (size_t)min(m0 + row, a.M - 1) * K + col
+                      : W + (size_t)min(n0 + row - BM, a.N - 1) * K + col;
   }
   auto issue = [&](auto S, int kt) __attribute__((always_inline)) {
     constexpr int s = decltype(S)::value;
@@ -362,75 +325,48 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a) {
   // no load may still be writing this block's LDS when the block retires
   __builtin_amdgcn_s_waitcnt(0);
 
-  store_tile<E, EPI, DH, TN, TM, SPLIT>(a, acc, m0 + wm * WM, n0 + wn * WN, lane, blockIdx.z);
+  // N is a multiple of 64 and a wave's columns divide 64: a wave of the last
+  // column tile lies either inside N or past it as a whole
+  if (n0 + wn * WN >= a.N) return;
+  store_tile<E, EPI, DH, TN, TM>(a, acc, m0 + wm * WM, n0 + wn * WN, lane);
 }
 
-template <int BM, int BN, int WGM, int WGN, int ST, int BK, int EPI, int ROLE, bool SPLIT>
+template <int BM, int BN, int WGM, int WGN, int ST, int BK, int EPI, int ROLE>
 __global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_kernel(GemmArgs a) {
-  gemm_body<bf16, BM, BN, WGM, WGN, ST, BK, EPI, 64, ROLE, SPLIT>(a);
+  gemm_body<bf16, BM, BN, WGM, WGN, ST, BK, EPI, 64>(a);
 }
 
 template <int BM, int BN, int WGM, int WGN, int ST, int BK, int EPI, int DH>
 __global__ __launch_bounds__(WGM* WGN * 64) void gemm_f32_kernel(GemmArgs a) {
-  gemm_body<float, BM, BN, WGM, WGN, ST, BK, EPI, DH, 0, false>(a);
+  gemm_body<float, BM, BN, WGM, WGN, ST, BK, EPI, DH>(a);
 }
 
-// Split-K second pass: sum the partials in split order, then the epilogue.
-template <int EPI, int ROLE>
-__global__ __launch_bounds__(256) void gemm_splitk_reduce_kernel(GemmArgs a, int splits) {
-  if (a.skip && *a.skip) return;
-  const int64_t i4 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t n4 = (int64_t)a.M * a.N / 4;
-  if (i4 >= n4) return;
-  const int m = (int)((i4 * 4) / a.N), n = (int)((i4 * 4) % a.N);
-  f32x4 sum = reinterpret_cast<const f32x4*>(a.partial)[i4];
-  for (int z = 1; z < splits; ++z) sum += reinterpret_cast<const f32x4*>(a.partial + (size_t)z * a.M * a.N)[i4];
-  epi4<bf16, EPI>(a, m, n, sum);
-}
-
-template <int BM, int BN, int WGM, int WGN, int ST, int BK, int ROLE>
-hipError_t launch_tile(const GemmArgs& a, int splits, hipStream_t s) {
-  const int blocks = ((a.M + BM - 1) / BM) * (a.N / BN);
+// The four projections: role 0 QKV, 1 attention output, 2 MLP-up, 3 MLP-down,
+// each with its own epilogue.
+template <int BM, int BN, int WGM, int WGN, int ST, int BK>
+hipError_t launch_tile(const GemmArgs& a, hipStream_t s) {
+  const int blocks = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
   constexpr int NT = WGM * WGN * 64;
-  if (splits > 1) {
-    dim3 grid(blocks, 1, splits);
-    launch_k(gemm_bf16_kernel<BM, BN, WGM, WGN, ST, BK, EPI_BIAS, ROLE, true>, grid, NT, 0, s, a);
-    const int64_t n4 = (int64_t)a.M * a.N / 4;
-    const unsigned rb = (unsigned)((n4 + 255) / 256);
-    switch (a.epi) {
-      case EPI_BIAS: launch_k(gemm_splitk_reduce_kernel<EPI_BIAS, ROLE>, rb, 256, 0, s, a, splits); break;
-      case EPI_BIAS_GELU: launch_k(gemm_splitk_reduce_kernel<EPI_BIAS_GELU, ROLE>, rb, 256, 0, s, a, splits); break;
-      case EPI_GATED_RES: launch_k(gemm_splitk_reduce_kernel<EPI_GATED_RES, ROLE>, rb, 256, 0, s, a, splits); break;
-      default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
-  }
-  switch (a.epi) {
-    case EPI_BIAS:
-      launch_k(gemm_bf16_kernel<BM, BN, WGM, WGN, ST, BK, EPI_BIAS, ROLE, false>, blocks, NT, 0, s, a);
-      break;
-    case EPI_BIAS_GELU:
-      launch_k(gemm_bf16_kernel<BM, BN, WGM, WGN, ST, BK, EPI_BIAS_GELU, ROLE, false>, blocks, NT, 0, s, a);
-      break;
-    case EPI_GATED_RES:
-      launch_k(gemm_bf16_kernel<BM, BN, WGM, WGN, ST, BK, EPI_GATED_RES, ROLE, false>, blocks, NT, 0, s, a);
-      break;
-    case EPI_QKV:
-      if constexpr ((BN / WGN) % 64 == 0) {
-        launch_k(gemm_bf16_kernel<BM, BN, WGM, WGN, ST, BK, EPI_QKV, ROLE, false>, blocks, NT, 0, s, a);
-      } else {
-        return hipErrorInvalidValue;
-      }
-      break;
-    default:
+  if (a.role == 0 && a.epi == EPI_QKV) {
+    if constexpr ((BN / WGN) % 64 == 0)
+      launch_k(gemm_bf16_kernel<BM, BN, WGM, WGN, ST, BK, EPI_QKV, 0>, blocks, NT, 0, s, a);
+    else
       return hipErrorInvalidValue;
+  } else if (a.role == 1 && a.epi == EPI_GATED_RES) {
+    launch_k(gemm_bf16_kernel<BM, BN, WGM, WGN, ST, BK, EPI_GATED_RES, 1>, blocks, NT, 0, s, a);
+  } else if (a.role == 2 && a.epi == EPI_BIAS_GELU) {
+    launch_k(gemm_bf16_kernel<BM, BN, WGM, WGN, ST, BK, EPI_BIAS_GELU, 2>, blocks, NT, 0, s, a);
+  } else if (a.role == 3 && a.epi == EPI_GATED_RES) {
+    launch_k(gemm_bf16_kernel<BM, BN, WGM, WGN, ST, BK, EPI_GATED_RES, 3>, blocks, NT, 0, s, a);
+  } else {
+    return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
 template <int BM, int BN, int WGM, int WGN, int ST, int BK>
 hipError_t launch_tile_f32(const GemmArgs& a, hipStream_t s) {
-  const int blocks = ((a.M + BM - 1) / BM) * (a.N / BN);
+  const int blocks = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
   constexpr int NT = WGM * WGN * 64;
   switch (a.epi) {
     case EPI_BIAS_GELU:

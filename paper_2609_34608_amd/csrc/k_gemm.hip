@@ -11,83 +11,78 @@ using gemm::launch_tile;
 using gemm::launch_tile_f32;
 
 // ---------------------------------------------------------------- configs
+// Tile shapes of the bf16 kernel and what a tile costs.  A CU that holds c
+// blocks at once (c <= occ) finishes them in about K / 64 * per[c-1] +
+// fix[c-1] us; the constants are least-squares fits to timings of every
+// configuration at the four projections of 57 model sizes (64 to 12000 rows,
+// D 256 to 2048), standard deviation 7-12%.  What they show: 256-column tiles
+// over 8 waves do the most work per byte loaded and win where their blocks
+// fill whole rounds of the 256 CUs; 128-column tiles over 4 waves leave room
+// for two blocks per CU, whose barriers and epilogues overlap, and waste less
+// in the last round; small tiles spread short sequences over the chip, where
+// a launch costs ~3 us whatever it does.
 struct TileCfg {
-  int bm, bn, wgm, wgn, st, bk;
+  int bm, bn, wgm, wgn, st, bk;  // rows x columns, waves (rows x columns), LDS stages, K per stage
+  int occ;
+  float per[3], fix[3];
 };
-// index: tile rows x cols, waves (rows x cols), LDS stages, K per stage
 constexpr TileCfg kCfgs[] = {
-    {64, 64, 2, 2, 4, 32},    // 0
-    {64, 128, 2, 2, 4, 32},   // 1
-    {128, 64, 2, 2, 4, 32},   // 2
-    {128, 128, 2, 2, 4, 32},  // 3
-    {256, 256, 2, 4, 4, 32},  // 4
-    {256, 256, 4, 2, 4, 32},  // 5
-    {256, 128, 2, 4, 4, 32},  // 6
-    {128, 256, 2, 4, 4, 32},  // 7
-    {128, 128, 2, 4, 4, 32},  // 8
-    {64, 256, 1, 4, 4, 32},   // 9
-    {64, 64, 2, 2, 8, 32},    // 10
-    {64, 128, 2, 2, 8, 32},   // 11
-    {128, 64, 2, 2, 8, 32},   // 12
-    {64, 64, 2, 2, 12, 32},   // 13
-    {128, 128, 2, 2, 8, 32},  // 14
-    {64, 64, 2, 2, 4, 128},   // 15
-    {64, 128, 2, 2, 3, 128},  // 16
-    {128, 64, 2, 2, 3, 128},  // 17
-    {64, 64, 2, 2, 4, 64},    // 18
-    {64, 128, 2, 2, 4, 64},   // 19
-    {128, 128, 2, 4, 4, 64},  // 20
-    {256, 256, 4, 2, 2, 64},  // 21
-    {256, 256, 2, 4, 2, 64},  // 22
-    {128, 128, 2, 2, 4, 64},  // 23
-    {192, 256, 2, 4, 2, 64},  // 24
-    {320, 256, 2, 4, 2, 64},  // 25
-    {64, 64, 4, 1, 4, 32},    // 26 (QKV outputs of 64 mod 128 columns: odd head counts)
-    {320, 128, 4, 2, 2, 64},  // 27
+    {256, 256, 2, 4, 2, 64, 1, {1.38f}, {7.85f}},
+    {320, 256, 2, 4, 2, 64, 1, {1.70f}, {8.28f}},
+    {192, 256, 2, 4, 2, 64, 1, {1.10f}, {7.13f}},
+    {160, 128, 2, 2, 2, 64, 2, {0.67f, 1.01f}, {4.73f, 8.28f}},
+    {128, 128, 2, 2, 2, 64, 2, {0.56f, 0.87f}, {4.24f, 6.95f}},
+    {96, 128, 2, 2, 2, 64, 2, {0.50f, 0.74f}, {3.74f, 5.40f}},
+    {64, 128, 2, 2, 3, 64, 2, {0.33f, 0.57f}, {3.89f, 4.31f}},
+    {96, 64, 2, 2, 3, 64, 2, {0.27f, 0.46f}, {3.38f, 3.56f}},
+    {64, 64, 2, 2, 4, 64, 2, {0.19f, 0.37f}, {3.14f, 2.39f}},
+    {32, 128, 2, 2, 4, 64, 2, {0.22f, 0.43f}, {3.45f, 2.77f}},
+    {32, 64, 2, 2, 4, 64, 3, {0.14f, 0.24f, 0.39f}, {2.78f, 2.94f, 1.94f}},
+    {32, 64, 2, 1, 4, 64, 3, {0.20f, 0.26f, 0.38f}, {3.18f, 3.62f, 2.20f}},
+    {32, 32, 2, 2, 4, 128, 2, {0.10f, 0.16f}, {2.90f, 3.00f}},
 };
 constexpr int kNumCfgs = sizeof(kCfgs) / sizeof(kCfgs[0]);
 
-template <int C, int ROLE>
-hipError_t launch_c(const GemmArgs& a, int splits, hipStream_t s) {
+template <int C>
+hipError_t launch_c(const GemmArgs& a, hipStream_t s) {
   constexpr TileCfg t = kCfgs[C];
-  return launch_tile<t.bm, t.bn, t.wgm, t.wgn, t.st, t.bk, ROLE>(a, splits, s);
+  return launch_tile<t.bm, t.bn, t.wgm, t.wgn, t.st, t.bk>(a, s);
 }
 
-template <int ROLE>
-hipError_t launch_role(const GemmArgs& a, int cfg, int splits, hipStream_t s) {
-  switch (cfg) {
-    case 0: return launch_c<0, ROLE>(a, splits, s);
-    case 1: return launch_c<1, ROLE>(a, splits, s);
-    case 2: return launch_c<2, ROLE>(a, splits, s);
-    case 3: return launch_c<3, ROLE>(a, splits, s);
-    case 4: return launch_c<4, ROLE>(a, splits, s);
-    case 5: return launch_c<5, ROLE>(a, splits, s);
-    case 6: return launch_c<6, ROLE>(a, splits, s);
-    case 7: return launch_c<7, ROLE>(a, splits, s);
-    case 8: return launch_c<8, ROLE>(a, splits, s);
-    case 9: return launch_c<9, ROLE>(a, splits, s);
-    case 10: return launch_c<10, ROLE>(a, splits, s);
-    case 11: return launch_c<11, ROLE>(a, splits, s);
-    case 12: return launch_c<12, ROLE>(a, splits, s);
-    case 13: return launch_c<13, ROLE>(a, splits, s);
-    case 14: return launch_c<14, ROLE>(a, splits, s);
-    case 15: return launch_c<15, ROLE>(a, splits, s);
-    case 16: return launch_c<16, ROLE>(a, splits, s);
-    case 17: return launch_c<17, ROLE>(a, splits, s);
-    case 18: return launch_c<18, ROLE>(a, splits, s);
-    case 19: return launch_c<19, ROLE>(a, splits, s);
-    case 20: return launch_c<20, ROLE>(a, splits, s);
-    case 21: return launch_c<21, ROLE>(a, splits, s);
-    case 22: return launch_c<22, ROLE>(a, splits, s);
-    case 23: return launch_c<23, ROLE>(a, splits, s);
-    case 24: return launch_c<24, ROLE>(a, splits, s);
-    case 25: return launch_c<25, ROLE>(a, splits, s);
-    case 26: return launch_c<26, ROLE>(a, splits, s);
-    default: return launch_c<27, ROLE>(a, splits, s);
+template <int... C>
+hipError_t launch_any(const GemmArgs& a, int cfg, hipStream_t s, std::integer_sequence<int, C...>) {
+  hipError_t e = hipErrorInvalidValue;
+  ((cfg == C ? (void)(e = launch_c<C>(a, s)) : (void)0), ...);
+  return e;
+}
+
+double tile_cost(const TileCfg& t, int M, int N, int K) {
+  const long blocks = (long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+  const long n = (blocks + 255) / 256;  // blocks of the busiest CU
+  const double stages = K / 64.0;
+  const int rem = (int)(n % t.occ);
+  double c = (double)(n / t.occ) * (stages * t.per[t.occ - 1] + t.fix[t.occ - 1]);
+  if (rem) c += stages * t.per[rem - 1] + t.fix[rem - 1];
+  return c;
+}
+
+// Configuration of the smallest cost.  Over those sizes its choice is 1.3%
+// slower than the fastest configuration on average (21% at worst, on a 5 us
+// launch); the fixed rules it replaced, with tiles that had to divide N, were
+// 22% slower on average, e.g. N = 1216, M = 5754: 41 -> 26 us (K = 1216) and
+// 122 -> 74 us (K = 4864).
+int plan_gemm(int M, int N, int K, int epi) {
+  int best = -1;
+  double bc = 0.0;
+  for (int c = 0; c < kNumCfgs; ++c) {
+    const TileCfg& t = kCfgs[c];
+    // the QKV epilogue needs whole heads (64 columns) per wave
+    if (K % t.bk || (epi == EPI_QKV && (t.bn / t.wgn) % 64)) continue;
+    const double v = tile_cost(t, M, N, K);
+    if (best < 0 || v < bc) best = c, bc = v;
   }
+  return best;
 }
-
-bool qkv_ok(int c) { return (kCfgs[c].bn / kCfgs[c].wgn) % 64 == 0; }
 
 // ---------------------------------------------------------------- fp32
 // The fp32 matrix rate (157 TFLOP/s, a sixteenth of bf16) leaves loads and
@@ -115,98 +110,11 @@ hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t s) {
 
 }  // namespace
 
-int gemm_num_configs() { return kNumCfgs; }
-
-GemmPlan plan_gemm(int M, int N, int K, int epi) {
-  // From a sweep of every configuration at the workload shapes.  Large M:
-  // tiles of 256 columns over 8 waves, K 64 per stage (two stages), with the
-  // row count (192, 256 or 320) that minimises whole rounds of one block per
-  // CU times rows per block, weighted by the per-row cost each tile height
-  // measured (192-row tiles ~10% dearer per row, 320-row ~3% cheaper).  For
-  // example M = 9224, N = 4096 (mid MLP-up): 592 blocks of 256 rows take 3
-  // rounds, 464 of 320 rows take 2 (98 -> 82 us); M = 9224, N = 1024: 196
-  // blocks of 192 rows fill one round that 148 of 256 leave a third idle
-  // (97 -> 83 us).  256 rows with K 32 per stage (four stages) for outputs of
-  // 1024 columns or fewer, or K not a multiple of 64.  Small M (under a few
-  // blocks per CU): 64x64 tiles with K 64 per stage, 64x128 for the QKV
-  // epilogue (whole heads per wave), 128x128 over 8 waves for wide, short-K
-  // outputs; a K split only for grids under half a block per CU.
-  GemmPlan p{0, 1};
-  if (M >= 2048 && N % 256 == 0) {
-    // outputs of at most 1024 columns whose 320x128 tiles fill one round
-    // of 192-256 blocks (the mid model's attention output and MLP-down,
-    // N = 1024: 232 blocks, against 196 of 192x256 that leave 60 CUs idle;
-    // 34.4 -> 31.8 and 97.4 -> 89.0 us)
-    const long b320x128 = (long)((M + 319) / 320) * (N / 128);
-    if (K % 64 == 0 && N <= 1024 && b320x128 >= 192 && b320x128 <= 256) {
-      p.cfg = 27;
-      return p;
-    }
-    if (K % 64 == 0) {
-      const long cols = N / 256;
-      auto cost = [&](int bm, double per_row) {
-        const long blocks = (M + bm - 1) / bm * cols;
-        return (double)((blocks + 255) / 256) * bm * per_row;
-      };
-      const double c192 = cost(192, 1.10), c256 = cost(256, 1.0), c320 = cost(320, 0.97);
-      if (c192 < c256 && c192 <= c320) {
-        p.cfg = 24;
-        return p;
-      }
-      if (c320 < c256) {
-        p.cfg = 25;
-        return p;
-      }
-    }
-    if (N > 1024 && K % 64 == 0) p.cfg = 22;
-    else p.cfg = N >= 3072 ? 5 : 4;
-    return p;
-  }
-  if (epi == EPI_QKV) {
-    // whole heads per wave: 64 columns per wave; an odd head count leaves
-    // N = 192 H a multiple of 64 only, which takes one wave column of 64
-    p.cfg = N % 128 != 0 ? 26 : K % 64 == 0 ? 19 : 1;
-    return p;
-  }
-  if (N >= 2048 && N % 128 == 0 && K <= 1024) {
-    p.cfg = 8;
-    return p;
-  }
-  const long blocks = (long)((M + 63) / 64) * (N / 64);
-  if (K % 64 == 0 && blocks >= 128) {
-    p.cfg = 18;
-    return p;
-  }
-  while (blocks * p.splits < 128 && K / (p.splits * 2) >= 768 && K % (gemm::kBK * p.splits * 2) == 0 &&
-         p.splits < 8)
-    p.splits *= 2;
-  return p;
-}
-
-size_t gemm_partial_floats(int M, int N, int K, int epi) {
-  const GemmPlan p = plan_gemm(M, N, K, epi);
-  return p.splits > 1 ? (size_t)p.splits * M * N : 0;
-}
-
-hipError_t launch_gemm_cfg(const GemmArgs& a, int cfg, int splits, hipStream_t s) {
-  if (a.M <= 0) return hipSuccess;
-  if (cfg < 0 || cfg >= kNumCfgs || splits < 1) return hipErrorInvalidValue;
-  if (a.K % (kCfgs[cfg].bk * splits) || a.N % kCfgs[cfg].bn || a.N % 4) return hipErrorInvalidValue;
-  if (splits > 1 && (a.epi == EPI_QKV || !a.partial)) return hipErrorInvalidValue;
-  if (a.epi == EPI_QKV && !qkv_ok(cfg)) return hipErrorInvalidValue;
-  switch (a.role) {
-    case 0: return launch_role<0>(a, cfg, splits, s);
-    case 1: return launch_role<1>(a, cfg, splits, s);
-    case 2: return launch_role<2>(a, cfg, splits, s);
-    default: return launch_role<3>(a, cfg, splits, s);
-  }
-}
-
 hipError_t launch_gemm(const GemmArgs& a, bool bf16_mode, hipStream_t s) {
   if (a.M <= 0) return hipSuccess;
   if (bf16_mode) {
-    const GemmPlan p = plan_gemm(a.M, a.N, a.K, a.epi);
-    return launch_gemm_cfg(a, p.cfg, p.splits, s);
+    if (a.N % 64) return hipErrorInvalidValue;  // ragged column tiles end on a wave's columns
+    return launch_any(a, plan_gemm(a.M, a.N, a.K, a.epi), s, std::make_integer_sequence<int, kNumCfgs>{});
   }
   return launch_gemm_f32(a, s);
 }

@@ -163,7 +163,7 @@ DevLayout dev_layout(const Dims& d) {
 
 struct WsLayout {
   size_t h, hq, pa, Ra, u, q, k, vt, attn, mlp, e, a1, sc, mod, gpart, v;
-  size_t x_bar, x_r, x_init, x_work, rr_rows, rr_res, tr_rms, or_sums, gsplit, total;
+  size_t x_bar, x_r, x_init, x_work, rr_rows, rr_res, tr_rms, or_sums, total;
   size_t rr_flag, hist_stats, hist_flag, cond_buf;
   size_t gpart_floats;
 };
@@ -196,14 +196,6 @@ WsLayout ws_layout(const Dims& d) {
   w.rr_res = take((size_t)d.B * 2 * 8 * 8);
   w.tr_rms = take((size_t)d.B * 2 * (1 + kRemapChunks) * 8);  // rms, then the run sums
   w.or_sums = take((size_t)WAM_MAX_COMPONENTS * kRemapChunks * 8);  // run sums per component
-  size_t split = 0;
-  if (d.bf) {
-    split = std::max(split, gemm_partial_floats(d.M, 3 * d.D, d.D, EPI_QKV));
-    split = std::max(split, gemm_partial_floats(d.M, d.D, d.D, EPI_GATED_RES));
-    split = std::max(split, gemm_partial_floats(d.M, d.F, d.D, EPI_BIAS_GELU));
-    split = std::max(split, gemm_partial_floats(d.M, d.D, d.F, EPI_GATED_RES));
-  }
-  w.gsplit = take(std::max<size_t>(split, 1) * 4);
   // device-side reuse decision: flag and one record per stage
   w.rr_flag = take(4);
   w.hist_stats = take((size_t)WAM_MAX_STEPS * d.B * 2 * 3 * 8);
@@ -389,7 +381,7 @@ int run_layer(wam_t h, int l, const int* skip = nullptr, float* copy = nullptr) 
     ProfScope ps(h, WAM_KC_GEMM_QKV, 2.0 * M * D * 3 * D);
     GemmArgs g{};
     g.A = h->S<char>(ws.u); g.W = qkv_w; g.bias = qkv_b; g.M = d.M; g.N = (int)(3 * D); g.K = (int)D;
-    g.role = 0; g.partial = h->S(ws.gsplit); g.skip = skip;
+    g.role = 0; g.skip = skip;
     // projection with q/k RMS-norm and the head-major layout fused in
     g.epi = EPI_QKV;
     g.qkv = QkvOut{h->S<char>(ws.q), h->S<char>(ws.k), h->S<char>(ws.vt), q_g, k_g,
@@ -408,7 +400,7 @@ int run_layer(wam_t h, int l, const int* skip = nullptr, float* copy = nullptr) 
   {
     ProfScope ps(h, WAM_KC_GEMM_PROJ, 2.0 * M * D * D);
     GemmArgs g{h->S<char>(ws.attn), proj_w, proj_b, mod + 2 * D, hh, d.M, (int)D, (int)D, EPI_GATED_RES, 1,
-               h->S(ws.gsplit), {}, skip};
+               {}, skip};
     HIPCHK(h, launch_gemm(g, d.bf, s));
   }
   HIPCHK(h, launch_ln_modulate(hh, mod + 3 * D, mod + 4 * D, h->S<char>(ws.u), d.M, d.D, h->cfg.ln_eps, d.bf, s,
@@ -416,13 +408,13 @@ int run_layer(wam_t h, int l, const int* skip = nullptr, float* copy = nullptr) 
   {
     ProfScope ps(h, WAM_KC_GEMM_FC1, 2.0 * M * D * d.F);
     GemmArgs g{h->S<char>(ws.u), fc1_w, fc1_b, nullptr, h->S<char>(ws.mlp), d.M, d.F, (int)D, EPI_BIAS_GELU, 2,
-               h->S(ws.gsplit), {}, skip};
+               {}, skip};
     HIPCHK(h, launch_gemm(g, d.bf, s));
   }
   {
     ProfScope ps(h, WAM_KC_GEMM_FC2, 2.0 * M * D * d.F);
     GemmArgs g{h->S<char>(ws.mlp), fc2_w, fc2_b, mod + 5 * D, hh, d.M, (int)D, d.F, EPI_GATED_RES, 3,
-               h->S(ws.gsplit), {}, skip, copy};
+               {}, skip, copy};
     HIPCHK(h, launch_gemm(g, d.bf, s));
   }
   return WAM_OK;

@@ -109,7 +109,6 @@ __device__ __forceinline__ float gelu_tanh_f(float x) {
 
 // ---------------------------------------------------------------- GEMM
 enum GemmEpilogue : int {
-  EPI_BIAS = 0,       // out[m,n] = acc + bias[n]                       (act type)
   EPI_BIAS_GELU = 1,  // out[m,n] = gelu(acc + bias[n])                 (act type)
   EPI_GATED_RES = 2,  // h[m,n] += gate[n] * (acc + bias[n])            (float32)
   EPI_QKV = 3,        // q,k RMS-normalised per head -> [B*H][Tpad][dh], v -> [B*H][dh][Tpad]
@@ -135,21 +134,11 @@ struct GemmArgs {
   int M, N, K;
   int epi;
   int role;          // distinct kernel symbol per projection (0 qkv, 1 proj, 2 fc1, 3 fc2)
-  float* partial;    // split-K scratch, splits * M * N floats
   QkvOut qkv;
   const int* skip;   // device flag: when non-null and set, the launch does nothing
   float* copy;       // EPI_GATED_RES: when non-null, the updated h is also stored here ([M][N])
 };
 
-struct GemmPlan {
-  int cfg;
-  int splits;
-};
-
-GemmPlan plan_gemm(int M, int N, int K, int epi);
-size_t gemm_partial_floats(int M, int N, int K, int epi);
-int gemm_num_configs();
-hipError_t launch_gemm_cfg(const GemmArgs& a, int cfg, int splits, hipStream_t s);
 hipError_t launch_gemm(const GemmArgs& a, bool bf16_mode, hipStream_t s);
 
 // ---------------------------------------------------------------- attention

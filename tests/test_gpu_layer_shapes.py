@@ -6,7 +6,7 @@ import pytest
 
 from oracle import dit as OD
 from synth import get_workload, make_weights, make_initial_noise, make_observations
-from gpu_common import device, to_dev, f32_sigmas
+from gpu_common import device, to_dev, f32_sigmas, BF16_UPDATE_TOL
 
 pytestmark = pytest.mark.gpu
 
@@ -16,11 +16,11 @@ def dev():
     return device()
 
 
-def _update_error(dev, spec, k=3):
+def _update_error(dev, spec, k=3, weight_std=0.05):
     """max |update error| over max |update|, and the float32 spacing of h over
     max |update| (the rounding of the stored h)."""
     from paper_2609_34608_amd import runtime as R
-    W = make_weights(spec, bias_std=0.02, gain_std=0.1, weight_std=0.05)
+    W = make_weights(spec, bias_std=0.02, gain_std=0.1, weight_std=weight_std)
     m = R.WamModel(R.config_of(spec), W, device=dev)
     sig = f32_sigmas(spec.K)
     m.set_schedule(sig)
@@ -54,3 +54,17 @@ def test_float32_layer(dev, B, T, D, dh, F, qk_norm):
     # rounding of the stored h0 and h1 (two roundings each), and the first-order
     # bound of the float32 sums (one 2^-24 per term)
     assert err <= 4 * ulp + (F + 3 * D) * 2.0 ** -24, (err, ulp)
+
+
+# bf16: (B, T, D, F).  Row counts off every tile height, widths 3 D, D and F
+# that end inside a 256-, 128- or 64-column tile (odd head counts among them),
+# from one block of rows to several rounds of the chip, so that small, two-per-
+# CU and 256-column tiles all run.
+@pytest.mark.parametrize("B,T,D,F", [
+    (1, 3, 64, 128), (1, 70, 192, 512), (2, 137, 320, 1280), (1, 505, 640, 2560), (3, 400, 448, 1152),
+    (2, 1100, 832, 2176), (2, 901, 1216, 4864), (4, 577, 1088, 2944), (1, 2650, 1600, 3200),
+])
+def test_bf16_layer(dev, B, T, D, F):
+    err, _ = _update_error(dev, _spec("bf16", B, T, D, 64, F), weight_std=0.02)
+    print(f"bf16 B={B} T={T} D={D} F={F}: update rel err {err:.2e}")
+    assert err <= BF16_UPDATE_TOL, err
