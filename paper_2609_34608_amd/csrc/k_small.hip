@@ -12,8 +12,6 @@ namespace wam {
 
 namespace {
 
-constexpr int kMaxVpl = 32;  // row kernels hold D/64 <= 32 values per lane
-
 __device__ __forceinline__ double block_sum_d(double v, double* sh) {
   v = wave_sum_d(v);
   const int w = threadIdx.x / kWave, lane = threadIdx.x % kWave;
@@ -204,89 +202,61 @@ __global__ __launch_bounds__(512) void embed_v4_kernel(EmbedArgs a) {
 }
 
 // ------------------------------------------------------------- LN + modulation
-// One wave per row; lane holds elements lane + 64 i.
-template <typename TOut>
-__global__ void ln_modulate_kernel(const float* __restrict__ h, const float* __restrict__ shift,
-                                   const float* __restrict__ scale, TOut* __restrict__ u,
-                                   int rows, int D, float eps, const int* skip) {
+// One wave per row; lane holds elements 4 lane + 256 i .. +3 (16-byte loads,
+// 8- or 16-byte stores), i < N4 = ceil(D / 256).  N4 is a template argument so
+// that the row and the modulation are fetched by 3 N4 loads issued together,
+// ahead of the reductions (with a run-time count the compiler emitted one load
+// and one wait per chunk).  RAG: D is not a multiple of 256 (it is one of 64),
+// and the lanes of the last chunk past D load the row's start again and count
+// as zero.  HBM bound (6 bytes an element); D = 1216, 5754 rows: 17.5 us
+// with one element per lane and load, 8.8 us here.
+template <int N4, bool RAG, typename TOut>
+__global__ __launch_bounds__(256) void ln_modulate_kernel(const float* __restrict__ h, const float* __restrict__ shift,
+                                                          const float* __restrict__ scale, TOut* __restrict__ u,
+                                                          int rows, int D, float eps, const int* skip) {
   if (skip && *skip) return;
+  if constexpr (!RAG) D = N4 * 256;
   const int row = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
   const int lane = threadIdx.x % kWave;
   if (row >= rows) return;
+  const int last = 4 * (lane + kWave * (N4 - 1));
+  const bool live = !RAG || last < D;  // of the last chunk
+  auto col = [&](int i) { return RAG && i == N4 - 1 && !live ? 0 : 4 * (lane + kWave * i); };
   const float* hr = h + (size_t)row * D;
-  const int vpl = D / kWave;
-  float v[kMaxVpl];
-  float s = 0.f;
-#pragma unroll
-  for (int i = 0; i < kMaxVpl; ++i) {
-    if (i < vpl) {
-      v[i] = hr[lane + kWave * i];
-      s += v[i];
-    }
-  }
-  const float mean = wave_sum(s) / (float)D;
-  float q = 0.f;
-#pragma unroll
-  for (int i = 0; i < kMaxVpl; ++i)
-    if (i < vpl) {
-      const float d = v[i] - mean;
-      q += d * d;
-    }
-  const float rstd = rsqrtf(wave_sum(q) / (float)D + eps);
-  TOut* ur = u + (size_t)row * D;
-#pragma unroll
-  for (int i = 0; i < kMaxVpl; ++i)
-    if (i < vpl) {
-      const int c = lane + kWave * i;
-      ur[c] = from_f32<TOut>((v[i] - mean) * rstd * (1.0f + scale[c]) + shift[c]);
-    }
-}
-
-// Vectorised form for D % 256 == 0 and bf16 output: lane holds
-// elements 4 lane + 256 i .. +3 (16-byte loads, 8-byte stores).  N4 = D / 256
-// is a template argument so that the row and the modulation are fetched by
-// 3 N4 loads issued together, ahead of the reductions (with a run-time count
-// the compiler emitted one load and one wait per chunk).
-template <int N4>
-__global__ __launch_bounds__(256) void ln_modulate_v4_kernel(const float* __restrict__ h, const float* __restrict__ shift,
-                                                             const float* __restrict__ scale, bf16* __restrict__ u,
-                                                             int rows, float eps, const int* skip) {
-  if (skip && *skip) return;
-  constexpr int D = N4 * 256;
-  const int row = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
-  const int lane = threadIdx.x % kWave;
-  if (row >= rows) return;
-  const f32x4* hr = reinterpret_cast<const f32x4*>(h + (size_t)row * D);
-  const f32x4* sc4 = reinterpret_cast<const f32x4*>(scale);
-  const f32x4* sh4 = reinterpret_cast<const f32x4*>(shift);
   f32x4 v[N4], sc[N4], sh[N4];
 #pragma unroll
-  for (int i = 0; i < N4; ++i) v[i] = hr[lane + kWave * i];
+  for (int i = 0; i < N4; ++i) v[i] = *reinterpret_cast<const f32x4*>(hr + col(i));
 #pragma unroll
   for (int i = 0; i < N4; ++i) {
-    sc[i] = sc4[lane + kWave * i];
-    sh[i] = sh4[lane + kWave * i];
+    sc[i] = *reinterpret_cast<const f32x4*>(scale + col(i));
+    sh[i] = *reinterpret_cast<const f32x4*>(shift + col(i));
   }
   __builtin_amdgcn_sched_barrier(0);  // keep the modulation loads ahead of the reductions
   float s = 0.f;
 #pragma unroll
-  for (int i = 0; i < N4; ++i) s += (v[i].x + v[i].y) + (v[i].z + v[i].w);
+  for (int i = 0; i < N4; ++i) {
+    const float t = (v[i].x + v[i].y) + (v[i].z + v[i].w);
+    s += i < N4 - 1 || live ? t : 0.f;
+  }
   const float mean = wave_sum(s) / (float)D;
   float q = 0.f;
 #pragma unroll
   for (int i = 0; i < N4; ++i) {
     const float a = v[i].x - mean, b = v[i].y - mean, c = v[i].z - mean, d = v[i].w - mean;
-    q += (a * a + b * b) + (c * c + d * d);
+    const float t = (a * a + b * b) + (c * c + d * d);
+    q += i < N4 - 1 || live ? t : 0.f;
   }
   const float rstd = rsqrtf(wave_sum(q) / (float)D + eps);
+  TOut* ur = u + (size_t)row * D;
 #pragma unroll
   for (int i = 0; i < N4; ++i) {
-    const int c = 4 * (lane + kWave * i);
-    bf16x4 o = {static_cast<bf16>((v[i].x - mean) * rstd * (1.0f + sc[i].x) + sh[i].x),
-                static_cast<bf16>((v[i].y - mean) * rstd * (1.0f + sc[i].y) + sh[i].y),
-                static_cast<bf16>((v[i].z - mean) * rstd * (1.0f + sc[i].z) + sh[i].z),
-                static_cast<bf16>((v[i].w - mean) * rstd * (1.0f + sc[i].w) + sh[i].w)};
-    *reinterpret_cast<bf16x4*>(u + (size_t)row * D + c) = o;
+    if (i == N4 - 1 && !live) break;
+    const f32x4 o = (v[i] - mean) * rstd * (1.0f + sc[i]) + sh[i];
+    if constexpr (sizeof(TOut) == 2)
+      *reinterpret_cast<bf16x4*>(ur + col(i)) = bf16x4{static_cast<bf16>(o[0]), static_cast<bf16>(o[1]),
+                                                       static_cast<bf16>(o[2]), static_cast<bf16>(o[3])};
+    else
+      *reinterpret_cast<f32x4*>(ur + col(i)) = o;
   }
 }
 
@@ -959,26 +929,34 @@ hipError_t launch_embed(const EmbedArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <int N4>
+void launch_ln_t(const float* h, const float* shift, const float* scale, void* u, int rows, int D, float eps,
+                 bool bf16_out, hipStream_t s, const int* skip) {
+  const int grid = (rows + 3) / 4;
+  bf16* ub = static_cast<bf16*>(u);
+  float* uf = static_cast<float*>(u);
+  if (D % 256 == 0) {
+    if (bf16_out) launch_k(ln_modulate_kernel<N4, false, bf16>, grid, 256, 0, s, h, shift, scale, ub, rows, D, eps, skip);
+    else launch_k(ln_modulate_kernel<N4, false, float>, grid, 256, 0, s, h, shift, scale, uf, rows, D, eps, skip);
+  } else {
+    if (bf16_out) launch_k(ln_modulate_kernel<N4, true, bf16>, grid, 256, 0, s, h, shift, scale, ub, rows, D, eps, skip);
+    else launch_k(ln_modulate_kernel<N4, true, float>, grid, 256, 0, s, h, shift, scale, uf, rows, D, eps, skip);
+  }
+}
+
 hipError_t launch_ln_modulate(const float* h, const float* shift, const float* scale, void* u,
                               int rows, int D, float eps, bool bf16_out, hipStream_t s, const int* skip) {
-  if (D % kWave || D / kWave > kMaxVpl) return hipErrorInvalidValue;
-  const int wpb = 4;
-  dim3 grid((rows + wpb - 1) / wpb);
-  if (bf16_out && D % 256 == 0 && D <= 2048) {
-    switch (D / 256) {
-      case 1: launch_k(ln_modulate_v4_kernel<1>, grid, wpb * kWave, 0, s, h, shift, scale, (bf16*)u, rows, eps, skip); break;
-      case 2: launch_k(ln_modulate_v4_kernel<2>, grid, wpb * kWave, 0, s, h, shift, scale, (bf16*)u, rows, eps, skip); break;
-      case 3: launch_k(ln_modulate_v4_kernel<3>, grid, wpb * kWave, 0, s, h, shift, scale, (bf16*)u, rows, eps, skip); break;
-      case 4: launch_k(ln_modulate_v4_kernel<4>, grid, wpb * kWave, 0, s, h, shift, scale, (bf16*)u, rows, eps, skip); break;
-      case 5: launch_k(ln_modulate_v4_kernel<5>, grid, wpb * kWave, 0, s, h, shift, scale, (bf16*)u, rows, eps, skip); break;
-      case 6: launch_k(ln_modulate_v4_kernel<6>, grid, wpb * kWave, 0, s, h, shift, scale, (bf16*)u, rows, eps, skip); break;
-      case 7: launch_k(ln_modulate_v4_kernel<7>, grid, wpb * kWave, 0, s, h, shift, scale, (bf16*)u, rows, eps, skip); break;
-      default: launch_k(ln_modulate_v4_kernel<8>, grid, wpb * kWave, 0, s, h, shift, scale, (bf16*)u, rows, eps, skip); break;
-    }
-  } else if (bf16_out)
-    launch_k(ln_modulate_kernel<bf16>, grid, wpb * kWave, 0, s, h, shift, scale, (bf16*)u, rows, D, eps, skip);
-  else
-    launch_k(ln_modulate_kernel<float>, grid, wpb * kWave, 0, s, h, shift, scale, (float*)u, rows, D, eps, skip);
+  if (D % kWave || D > 2048) return hipErrorInvalidValue;
+  switch ((D + 255) / 256) {
+    case 1: launch_ln_t<1>(h, shift, scale, u, rows, D, eps, bf16_out, s, skip); break;
+    case 2: launch_ln_t<2>(h, shift, scale, u, rows, D, eps, bf16_out, s, skip); break;
+    case 3: launch_ln_t<3>(h, shift, scale, u, rows, D, eps, bf16_out, s, skip); break;
+    case 4: launch_ln_t<4>(h, shift, scale, u, rows, D, eps, bf16_out, s, skip); break;
+    case 5: launch_ln_t<5>(h, shift, scale, u, rows, D, eps, bf16_out, s, skip); break;
+    case 6: launch_ln_t<6>(h, shift, scale, u, rows, D, eps, bf16_out, s, skip); break;
+    case 7: launch_ln_t<7>(h, shift, scale, u, rows, D, eps, bf16_out, s, skip); break;
+    default: launch_ln_t<8>(h, shift, scale, u, rows, D, eps, bf16_out, s, skip); break;
+  }
   return hipGetLastError();
 }
 
