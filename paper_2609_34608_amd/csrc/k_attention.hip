@@ -181,7 +181,10 @@ __global__ __launch_bounds__(NW * KSPLIT * 64) void attn_bf16_kernel(AttnArgs a)
         }
     }
     if constexpr (!BND) {
-    // online softmax per query column (lane-local except the max)
+    // online softmax per query column.  A lane looks at its own 16 keys only:
+    // m moves when some lane's maximum is more than 8 above it, so that the
+    // usual tile has no cross-lane step (with two shuffles per query tile here
+    // T = 4320, 16 heads took 119 us, without them 107)
     float mx[QT];
     bool grow = false;
 #pragma unroll
@@ -191,16 +194,15 @@ __global__ __launch_bounds__(NW * KSPLIT * 64) void attn_bf16_kernel(AttnArgs a)
       for (int kt = 0; kt < 4; ++kt)
 #pragma unroll
         for (int r = 0; r < 4; ++r) m = fmaxf(m, s[kt][qt][r]);
-      m = fmaxf(m, __shfl_xor(m, 16, 64));
-      m = fmaxf(m, __shfl_xor(m, 32, 64));
       mx[qt] = m;
       grow = grow || m > 8.0f;
     }
-    // move m when this tile raises some query's max by more than 8 (one
-    // wave-uniform branch for all query tiles), and always on the first tile
+    // one wave-uniform branch for all query tiles; the first tile always sets m
     if (first || __builtin_amdgcn_ballot_w64(grow) != 0) {
 #pragma unroll
       for (int qt = 0; qt < QT; ++qt) {
+        mx[qt] = fmaxf(mx[qt], __shfl_xor(mx[qt], 16, 64));
+        mx[qt] = fmaxf(mx[qt], __shfl_xor(mx[qt], 32, 64));
         const float delta = first ? mx[qt] : fmaxf(mx[qt], 0.f);
         // first tile: O and l are still zero, any finite factor keeps them so
         const float corr = __builtin_amdgcn_exp2f(fminf(-delta, 0.f));
@@ -935,7 +937,6 @@ hipError_t launch_attention_cfg(const AttnArgs& a, int qt, int nw, int st, hipSt
       switch (key) {
         case 10404: launch_k(attn_bf16_bounded_kernel<1, 4, 4>, grid, 256, 0, s, a); break;
         case 20404: launch_k(attn_bf16_bounded_kernel<2, 4, 4>, grid, 256, 0, s, a); break;
-        case 20403: launch_k(attn_bf16_bounded_kernel<2, 4, 3>, grid, 256, 0, s, a); break;
         default: return hipErrorInvalidValue;
       }
       break;
@@ -947,8 +948,9 @@ hipError_t launch_attention_cfg(const AttnArgs& a, int qt, int nw, int st, hipSt
       break;
     case ATTN_PLAIN:
       switch (key) {
+        case 10402: launch_k(attn_bf16_kernel<1, 4, 2, true>, grid, 256, 0, s, a); break;
         case 20402: launch_k(attn_bf16_kernel<2, 4, 2, true>, grid, 256, 0, s, a); break;
-        case 20403: launch_k(attn_bf16_kernel<2, 4, 3, true>, grid, 256, 0, s, a); break;
+        case 30402: launch_k(attn_bf16_kernel<3, 4, 2, true>, grid, 256, 0, s, a); break;
         case 40802: launch_k(attn_bf16_kernel<4, 8, 2, true>, grid, 512, 0, s, a); break;
         default: return hipErrorInvalidValue;
       }
@@ -956,20 +958,15 @@ hipError_t launch_attention_cfg(const AttnArgs& a, int qt, int nw, int st, hipSt
     case ATTN_PINGPONG:
       switch (key) {
         case 40804: launch_k(attn_bf16_pingpong_kernel<4, 4>, grid, 512, 0, s, a); break;
-        case 20804: launch_k(attn_bf16_pingpong_kernel<2, 4>, grid, 512, 0, s, a); break;
         default: return hipErrorInvalidValue;
       }
       break;
     default:
       switch (key) {
-        case 10404: launch_k(attn_bf16_kernel<1, 4, 4>, grid, 256, 0, s, a); break;
-        case 20404: launch_k(attn_bf16_kernel<2, 4, 4>, grid, 256, 0, s, a); break;
-        case 40403: launch_k(attn_bf16_kernel<4, 4, 3>, grid, 256, 0, s, a); break;
-        case 10804: launch_k(attn_bf16_kernel<1, 8, 4>, grid, 512, 0, s, a); break;
-        case 20804: launch_k(attn_bf16_kernel<2, 8, 4>, grid, 512, 0, s, a); break;
-        case 20803: launch_k(attn_bf16_kernel<2, 8, 3>, grid, 512, 0, s, a); break;
-        case 40402: launch_k(attn_bf16_kernel<4, 4, 2>, grid, 256, 0, s, a); break;
+        case 10402: launch_k(attn_bf16_kernel<1, 4, 2>, grid, 256, 0, s, a); break;
         case 20402: launch_k(attn_bf16_kernel<2, 4, 2>, grid, 256, 0, s, a); break;
+        case 30402: launch_k(attn_bf16_kernel<3, 4, 2>, grid, 256, 0, s, a); break;
+        case 30802: launch_k(attn_bf16_kernel<3, 8, 2>, grid, 512, 0, s, a); break;
         default: return hipErrorInvalidValue;
       }
   }
@@ -998,30 +995,64 @@ hipError_t launch_attention_f32(const AttnArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Forms that the automatic choice picks from, and what a block costs: a CU
+// that holds c of its blocks at once (c <= occ, set by their registers) takes
+// about ceil(T / 64) * per[c-1] + fix[c-1] us, least-squares fits to timings
+// of every form at 52 sizes (B 1 to 16, 4 to 32 heads, T 64 to 12000; standard
+// deviation 4-10%).  More queries per wave share each K / V^T read but leave
+// larger remainders in the last round; short sequences of few heads split the
+// keys over two groups of four waves (T = 864, 12 heads: 8.4 us against 8.9).
+struct AttnCfg {
+  AttnForm form;
+  int qt, nw, occ;
+  float per[5], fix[5];
+};
+constexpr AttnCfg kBounded[] = {
+    {ATTN_PLAIN, 4, 8, 1, {1.53f}, {5.0f}},
+    {ATTN_PLAIN, 3, 4, 2, {0.84f, 1.19f}, {3.8f, 5.8f}},
+    {ATTN_PLAIN, 2, 4, 3, {0.62f, 0.87f, 1.24f}, {3.6f, 5.2f, 5.8f}},
+    {ATTN_PLAIN, 1, 4, 5, {0.41f, 0.60f, 0.78f, 1.07f, 1.29f}, {3.2f, 3.8f, 4.7f, 4.9f, 3.4f}},
+    {ATTN_PLAIN_KSPLIT, 1, 4, 2, {0.31f, 0.51f}, {3.9f, 3.8f}},
+};
+constexpr AttnCfg kRunning[] = {
+    {ATTN_RUNNING, 3, 8, 1, {1.37f}, {3.9f}},
+    {ATTN_RUNNING, 3, 4, 2, {0.86f, 1.32f}, {4.4f, 6.9f}},
+    {ATTN_RUNNING, 2, 4, 2, {0.61f, 0.94f}, {4.1f, 5.7f}},
+    {ATTN_RUNNING, 1, 4, 4, {0.50f, 0.64f, 0.89f, 1.05f}, {3.3f, 4.2f, 4.7f, 4.8f}},
+};
+
+// The form of the smallest cost: over those sizes 1.7% (bounded) and 1.0%
+// (running max) slower than the fastest form on average, where the fixed
+// rules before were 5% and 10%.
+template <int N>
+hipError_t launch_cheapest(const AttnArgs& a, const AttnCfg (&cfgs)[N], hipStream_t s) {
+  const AttnCfg* best = nullptr;
+  double bc = 0.0;
+  for (const AttnCfg& c : cfgs) {
+    const int qb = c.qt * c.nw * 16;
+    const long blocks = (long)((a.T + qb - 1) / qb) * a.B * a.H, n = (blocks + 255) / 256;
+    const int rem = (int)(n % c.occ), tiles = a.Tpad / kKB;
+    double v = (double)(n / c.occ) * (tiles * c.per[c.occ - 1] + c.fix[c.occ - 1]);
+    if (rem) v += tiles * c.per[rem - 1] + c.fix[rem - 1];
+    if (!best || v < bc) best = &c, bc = v;
+  }
+  return launch_attention_cfg(a, best->qt, best->nw, 2, s, best->form);
+}
+
 hipError_t launch_attention(const AttnArgs& a, bool bf16_mode, hipStream_t s) {
   if (bf16_mode && a.bounded && a.variant != WAM_ATTN_RUNNING_MAX) {
+    if (a.variant == WAM_ATTN_AUTO) return launch_cheapest(a, kBounded, s);
     if (a.variant == WAM_ATTN_PINGPONG) return launch_attention_cfg(a, 4, 8, 4, s, ATTN_PINGPONG);
-    // from a sweep at the workload shapes: long sequences with about two
-    // blocks of 512 queries per CU take 8 waves of 64 queries; 4 waves of 32
-    // queries when that fills the chip; short grids (T = 864, 12 heads: 168
-    // blocks) two groups of 4 waves of 16 queries that split the keys (8.5
-    // against 9.3 us), unless there are too few key tiles to split
+    // forms asked for by name
     const bool big = a.T >= 4096 && (long)((a.T + 511) / 512) * a.B * a.H >= 384;
     const bool full = (long)((a.T + 127) / 128) * a.B * a.H >= 256;
     if (a.variant == WAM_ATTN_BOUNDED)
       return full ? launch_attention_cfg(a, 2, 4, 4, s, ATTN_PIPELINED) : launch_attention_cfg(a, 1, 4, 4, s, ATTN_PIPELINED);
     if (big) return launch_attention_cfg(a, 4, 8, 2, s, ATTN_PLAIN);
     if (full) return launch_attention_cfg(a, 2, 4, 2, s, ATTN_PLAIN);
-    if (a.variant == WAM_ATTN_PLAIN || a.Tpad / kKB >= 4) return launch_attention_cfg(a, 1, 4, 2, s, ATTN_PLAIN_KSPLIT);
-    return launch_attention_cfg(a, 1, 4, 4, s, ATTN_PIPELINED);
+    return launch_attention_cfg(a, 1, 4, 2, s, ATTN_PLAIN_KSPLIT);
   }
-  if (bf16_mode) {
-    // 4 waves x 32 queries (two K/V stages) when that fills the chip, else
-    // 4 waves x 16 queries
-    const long blocks = (long)((a.T + 255) / 256) * a.B * a.H;
-    if (blocks >= 256) return launch_attention_cfg(a, 2, 4, 2, s, ATTN_RUNNING);
-    return launch_attention_cfg(a, 1, 4, 4, s, ATTN_RUNNING);
-  }
+  if (bf16_mode) return launch_cheapest(a, kRunning, s);
   // fp32: enough 16-query tiles for two waves per SIMD without a key split
   // (2048 waves), else four waves split the keys of one tile; two tiles per
   // wave (half the K / V^T traffic) once that still leaves four waves per SIMD

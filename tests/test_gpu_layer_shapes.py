@@ -68,3 +68,17 @@ def test_bf16_layer(dev, B, T, D, F):
     err, _ = _update_error(dev, _spec("bf16", B, T, D, 64, F), weight_std=0.02)
     print(f"bf16 B={B} T={T} D={D} F={F}: update rel err {err:.2e}")
     assert err <= BF16_UPDATE_TOL, err
+
+
+# bf16 attention forms of the automatic choice, bounded (QK-norm) and running
+# max (without): (B, T, D).  Short sequences of few heads (key split, 16 queries
+# per wave) to grids of several blocks per CU (32, 48 and 64 queries per wave),
+# lengths off every block of queries; the scores of the unnormalised model
+# spread over tens of log2 units, so the running max moves.
+@pytest.mark.parametrize("qk_norm", [True, False])
+@pytest.mark.parametrize("B,T,D", [(1, 37, 64), (1, 449, 320), (4, 333, 1024), (16, 150, 512), (1, 2211, 512),
+                                   (2, 1130, 1088)])
+def test_bf16_attention_forms(dev, B, T, D, qk_norm):
+    err, _ = _update_error(dev, _spec("bf16", B, T, D, 64, 2 * D, qk_norm), weight_std=0.02 if qk_norm else 0.045)
+    print(f"bf16 attention B={B} T={T} D={D} qk_norm={qk_norm}: update rel err {err:.2e}")
+    assert err <= BF16_UPDATE_TOL, err
