@@ -411,39 +411,6 @@ __global__ __launch_bounds__(NW * 64) void final_kernel(FinalArgs a) {
 
 
 // ------------------------------------------------------------- Residual Rescaling
-// Per row: sums of p_i p_a, p_i^2, p_a^2 with p_i = h_s - h_q (float64), one
-// wave per row (any D multiple of 4); rr_finish_kernel reduces them.
-__global__ void rr_row_sums_kernel(const float* __restrict__ hs, const float* __restrict__ hq,
-                                       const float* __restrict__ pa, double* __restrict__ out,
-                                       int rows, int D) {
-  const int row = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
-  const int lane = threadIdx.x % kWave;
-  if (row >= rows) return;
-  const size_t off = (size_t)row * D;
-  double sip = 0.0, sii = 0.0, saa = 0.0;
-  for (int c = lane * 4; c < D; c += kWave * 4) {
-    const float4 s4 = *reinterpret_cast<const float4*>(hs + off + c);
-    const float4 q4 = *reinterpret_cast<const float4*>(hq + off + c);
-    const float4 a4 = *reinterpret_cast<const float4*>(pa + off + c);
-    const float pi[4] = {s4.x - q4.x, s4.y - q4.y, s4.z - q4.z, s4.w - q4.w};
-    const float pv[4] = {a4.x, a4.y, a4.z, a4.w};
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      sip += (double)pi[j] * pv[j];
-      sii += (double)pi[j] * pi[j];
-      saa += (double)pv[j] * pv[j];
-    }
-  }
-  sip = wave_sum_d(sip);
-  sii = wave_sum_d(sii);
-  saa = wave_sum_d(saa);
-  if (lane == 0) {
-    out[(size_t)row * 3 + 0] = sip;
-    out[(size_t)row * 3 + 1] = sii;
-    out[(size_t)row * 3 + 2] = saa;
-  }
-}
-
 // alpha (Eq. crr-alpha), cos and relative fit error (Eq. crr-gate) of one
 // (sample, branch) from its float64 sums over nrows rows of D elements.
 __device__ void rr_gate_stats(const RRGateArgs& a, int b, int br, int nrows, double sip, double sii, double saa) {
@@ -456,15 +423,15 @@ __device__ void rr_gate_stats(const RRGateArgs& a, int b, int br, int nrows, dou
   const double r2 = fmax(sii - 2.0 * alpha * sip + alpha * alpha * saa, 0.0);
   const double fit = sii > 0.0 ? sqrt(r2) / sqrt(sii) : INFINITY;
   const bool pass = ok_norm && cosv >= (double)a.gamma_cos && fit <= (double)a.gamma_fit;
-  double* r = a.result + ((size_t)b * 2 + br) * 8;
-  r[0] = sip;
-  r[1] = sii;
-  r[2] = saa;
-  r[3] = alpha;
-  r[4] = cosv;
-  r[5] = fit;
-  r[6] = pass ? 1.0 : 0.0;
-  r[7] = 0.0;
+  const double v[8] = {sip, sii, saa, alpha, cosv, fit, pass ? 1.0 : 0.0, 0.0};
+  const size_t at = ((size_t)b * 2 + br) * 8;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) a.result[at + i] = v[i];
+  // a host that decides reads them from its pinned buffer once the stream has
+  // drained, without a copy command between the gate and that wait
+  if (a.host)
+#pragma unroll
+    for (int i = 0; i < 8; ++i) a.host[at + i] = v[i];
 }
 
 // The gate in two launches, both in fixed summation orders.  Partials: blocks
@@ -472,7 +439,8 @@ __device__ void rr_gate_stats(const RRGateArgs& a, int b, int br, int nrows, dou
 // over the rows of branch 0 (rows [0, Nv) then [Nv+Na, T), nV = T - Na of
 // them) followed by gA = ceil(Na / 4) over branch 1 (rows [Nv, Nv+Na)).  Wave
 // w of a block takes one row (all of its loads issued before any
-// arithmetic), and the block adds its rows in wave order into one partial
+// arithmetic; lanes past D, a multiple of 64, take no part in the last chunk),
+// and the block adds its rows in wave order into one partial
 // (row_sums[block][3]).  The second kernel, one block per (sample, branch),
 // adds that pair's partials in block order and writes the statistics.
 template <int MAXV>
@@ -489,21 +457,20 @@ __global__ __launch_bounds__(256) void rr_gate_partials_kernel(RRGateArgs a) {
   double sip = 0.0, sii = 0.0, saa = 0.0;
   if (valid) {
     const size_t off = ((size_t)b * a.T + t) * a.D;
-    const int nv = a.D / (4 * kWave);
     const f32x4* s4 = reinterpret_cast<const f32x4*>(a.hs + off);
     const f32x4* q4 = reinterpret_cast<const f32x4*>(a.hq + off);
     const f32x4* a4 = reinterpret_cast<const f32x4*>(a.pa + off);
     f32x4 sv[MAXV], qv[MAXV], av[MAXV];
 #pragma unroll
     for (int k = 0; k < MAXV; ++k)
-      if (k < nv) {
+      if (4 * (lane + kWave * k) < a.D) {
         sv[k] = s4[lane + kWave * k];
         qv[k] = q4[lane + kWave * k];
         av[k] = a4[lane + kWave * k];
       }
 #pragma unroll
     for (int k = 0; k < MAXV; ++k)
-      if (k < nv) {
+      if (4 * (lane + kWave * k) < a.D) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const double pi = (double)(sv[k][e] - qv[k][e]), pv = (double)av[k][e];
@@ -554,39 +521,6 @@ __global__ __launch_bounds__(256) void rr_gate_finish_kernel(RRGateArgs a) {
   if (threadIdx.x == 0)
     rr_gate_stats(a, b, br, br ? a.Na : nV, (sh[0][0] + sh[0][1]) + (sh[0][2] + sh[0][3]),
                   (sh[1][0] + sh[1][1]) + (sh[1][2] + sh[1][3]), (sh[2][0] + sh[2][1]) + (sh[2][2] + sh[2][3]));
-}
-
-// One block per (sample, branch): alpha (Eq. crr-alpha), cos and relative
-// fit error (Eq. crr-gate) from the float64 row sums.
-__global__ __launch_bounds__(1024) void rr_finish_kernel(RRGateArgs a) {
-  const int b = blockIdx.x / 2, br = blockIdx.x % 2;
-  __shared__ double sh[3][16];
-  double s[3] = {0.0, 0.0, 0.0};
-  // branch rows as one index range: A = [Nv, Nv+Na); V = [0, Nv) then [Nv+Na, T)
-  const int nrows = br == 1 ? a.Na : a.T - a.Na;
-  const double* base = a.row_sums + (size_t)b * a.T * 3;
-#pragma unroll 4
-  for (int i = threadIdx.x; i < nrows; i += blockDim.x) {
-    const int t = br == 1 ? a.Nv + i : (i < a.Nv ? i : i + a.Na);
-    s[0] += base[(size_t)t * 3 + 0];
-    s[1] += base[(size_t)t * 3 + 1];
-    s[2] += base[(size_t)t * 3 + 2];
-  }
-  const int w = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-  for (int j = 0; j < 3; ++j) {
-    const double v = wave_sum_d(s[j]);
-    if (lane == 0) sh[j][w] = v;
-  }
-  __syncthreads();
-  if (threadIdx.x != 0) return;
-  const int nw = blockDim.x / kWave;
-  double sip = 0.0, sii = 0.0, saa = 0.0;
-  for (int i = 0; i < nw; ++i) {
-    sip += sh[0][i];
-    sii += sh[1][i];
-    saa += sh[2][i];
-  }
-  rr_gate_stats(a, b, br, nrows, sip, sii, saa);
 }
 
 // h_e = h_s + alpha_{b,branch} R_a (Eq. residual-injection), in place on h.
@@ -860,13 +794,14 @@ struct OrSumArgs {
   const float* u[WAM_MAX_COMPONENTS];
   int64_t n[WAM_MAX_COMPONENTS];
   double inv_delta[WAM_MAX_COMPONENTS];
+  int vec;  // bit m: component m takes 16-byte loads
   double* sums;
 };
 
 // Run sums of ((u_hat - u) / delta)^2 of component blockIdx.y, run blockIdx.x
 // of reduce_chunks(n) runs of whole 4-element groups (float64, the order of
-// run_sq_sum); the host adds the runs in order.
-template <bool VEC>
+// run_sq_sum), stored straight into the host's pinned buffer; the host adds the
+// runs in order.
 __global__ __launch_bounds__(256) void or_sums_kernel(OrSumArgs a) {
   __shared__ double sh[16];
   const int m = blockIdx.y;
@@ -876,7 +811,8 @@ __global__ __launch_bounds__(256) void or_sums_kernel(OrSumArgs a) {
   const int64_t ng = (n + 3) / 4, per = (ng + nch - 1) / nch;
   const int64_t g0 = (int64_t)blockIdx.x * per;
   const int64_t g1 = g0 + per < ng ? g0 + per : ng;
-  double s = run_sq_sum<VEC>(a.u_hat[m], a.u[m], a.inv_delta[m], g0, g1, n);
+  double s = a.vec >> m & 1 ? run_sq_sum<true>(a.u_hat[m], a.u[m], a.inv_delta[m], g0, g1, n)
+                            : run_sq_sum<false>(a.u_hat[m], a.u[m], a.inv_delta[m], g0, g1, n);
   s = block_sum_d(s, sh);
   if (threadIdx.x == 0) a.sums[(size_t)m * kRemapChunks + blockIdx.x] = s;
 }
@@ -999,17 +935,10 @@ hipError_t launch_final(const FinalArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_rr_gate(const RRGateArgs& a, hipStream_t s) {
-  const int rows = a.B * a.T;
-  if (a.D % 4) return hipErrorInvalidValue;
-  const int wpb = 4;
-  if (a.D % 256 == 0 && a.D <= 2048) {
-    const int per = (a.T - a.Na + 3) / 4 + (a.Na + 3) / 4;
-    launch_k(rr_gate_partials_kernel<8>, (unsigned)(a.B * per), 256, 0, s, a);
-    launch_k(rr_gate_finish_kernel, (unsigned)(a.B * 2), 256, 0, s, a);
-    return hipGetLastError();
-  }
-  launch_k(rr_row_sums_kernel, (rows + wpb - 1) / wpb, wpb * kWave, 0, s, a.hs, a.hq, a.pa, a.row_sums, rows, a.D);
-  launch_k(rr_finish_kernel, a.B * 2, 1024, 0, s, a);
+  if (a.D % kWave || a.D > 2048) return hipErrorInvalidValue;
+  const int per = (a.T - a.Na + 3) / 4 + (a.Na + 3) / 4;
+  launch_k(rr_gate_partials_kernel<8>, (unsigned)(a.B * per), 256, 0, s, a);
+  launch_k(rr_gate_finish_kernel, (unsigned)(a.B * 2), 256, 0, s, a);
   return hipGetLastError();
 }
 
@@ -1091,21 +1020,17 @@ hipError_t launch_or_sums(int n_comp, const float* const* u_hat, const float* co
                           const int64_t* n, const double* delta, double* sums, hipStream_t s) {
   if (n_comp < 1 || n_comp > WAM_MAX_COMPONENTS) return hipErrorInvalidValue;
   OrSumArgs a{};
-  bool vec = true;
   for (int m = 0; m < n_comp; ++m) {
     a.u_hat[m] = u_hat[m];
     a.u[m] = u[m];
     a.n[m] = n[m];
     a.inv_delta[m] = 1.0 / delta[m];
-    vec = vec && aligned16(u_hat[m]) && aligned16(u[m]) && n[m] % 4 == 0;
+    if (aligned16(u_hat[m]) && aligned16(u[m]) && n[m] % 4 == 0) a.vec |= 1 << m;
   }
   a.sums = sums;
   int nch = 1;
   for (int m = 0; m < n_comp; ++m) nch = std::max(nch, reduce_chunks(n[m]));
-  if (vec)
-    launch_k(or_sums_kernel<true>, dim3(nch, n_comp), 256, 0, s, a);
-  else
-    launch_k(or_sums_kernel<false>, dim3(nch, n_comp), 256, 0, s, a);
+  launch_k(or_sums_kernel, dim3(nch, n_comp), 256, 0, s, a);
   return hipGetLastError();
 }
 

@@ -163,7 +163,7 @@ DevLayout dev_layout(const Dims& d) {
 
 struct WsLayout {
   size_t h, hq, pa, Ra, u, q, k, vt, attn, mlp, e, a1, sc, mod, gpart, v;
-  size_t x_bar, x_r, x_init, x_work, rr_rows, rr_res, tr_rms, or_sums, total;
+  size_t x_bar, x_r, x_init, x_work, rr_rows, rr_res, tr_rms, total;
   size_t rr_flag, hist_stats, hist_flag, cond_buf;
   size_t gpart_floats;
 };
@@ -195,7 +195,6 @@ WsLayout ws_layout(const Dims& d) {
   w.rr_rows = take((size_t)d.M * 3 * 8);
   w.rr_res = take((size_t)d.B * 2 * 8 * 8);
   w.tr_rms = take((size_t)d.B * 2 * (1 + kRemapChunks) * 8);  // rms, then the run sums
-  w.or_sums = take((size_t)WAM_MAX_COMPONENTS * kRemapChunks * 8);  // run sums per component
   // device-side reuse decision: flag and one record per stage
   w.rr_flag = take(4);
   w.hist_stats = take((size_t)WAM_MAX_STEPS * d.B * 2 * 3 * 8);
@@ -491,7 +490,7 @@ int enqueue_step_device(wam_t h, int k, const float* x, const float* cond, float
   const int* flag = nullptr;
   if (attempt) {
     const RRRows br = rr_rows(d, rr);
-    RRGateArgs g{hh, h->S(ws.hq), h->S(ws.pa), h->S<double>(ws.rr_rows), h->S<double>(ws.rr_res),
+    RRGateArgs g{hh, h->S(ws.hq), h->S(ws.pa), h->S<double>(ws.rr_rows), h->S<double>(ws.rr_res), nullptr,
                  d.B, d.T, d.D, br.nv, br.na, rr->alpha_min, rr->alpha_max, rr->eps, rr->gamma_cos,
                  rr->gamma_fit};
     {
@@ -610,15 +609,13 @@ int forward(wam_t h, int k, const float* x, const float* cond, float* v_out, flo
     const RRRows br = rr_rows(d, rr);
     if (h->layer_valid && (rr->mode == WAM_RR_AUTO || rr->mode == WAM_RR_FORCE_SKIP)) {
       in->rr_attempted = 1;
-      RRGateArgs g{hh, h->S(ws.hq), h->S(ws.pa), h->S<double>(ws.rr_rows), h->S<double>(ws.rr_res),
+      RRGateArgs g{hh, h->S(ws.hq), h->S(ws.pa), h->S<double>(ws.rr_rows), h->S<double>(ws.rr_res), h->host_stage,
                    d.B, d.T, d.D, br.nv, br.na, rr->alpha_min, rr->alpha_max, rr->eps, rr->gamma_cos,
                    rr->gamma_fit};
       {
         ProfScope ps(h, WAM_KC_RR_GATE, 3.0 * MD * 4);
         HIPCHK(h, launch_rr_gate(g, s));
       }
-      const size_t nres = (size_t)d.B * 2 * 8;
-      HIPCHK(h, hipMemcpyAsync(h->host_stage, h->S<double>(ws.rr_res), nres * 8, hipMemcpyDeviceToHost, s));
       HIPCHK(h, hipStreamSynchronize(s));
       bool all = true;
       for (int b = 0; b < d.B; ++b)
@@ -819,10 +816,12 @@ int wam_init(const wam_config* cfg, const float* hw, size_t n_hw, void* dev_weig
   h->wdev = static_cast<char*>(dev_weights);
   h->wsdev = static_cast<char*>(dev_ws);
   h->stream = static_cast<hipStream_t>(stream);
-  // gate statistics (B x 2 x 8 doubles) or the score's run sums (components x runs)
+  // gate statistics (B x 2 x 8 doubles) or the score's run sums (components x
+  // runs), stored there by the kernels
   constexpr size_t kStageBytes = (size_t)WAM_MAX_COMPONENTS * kRemapChunks * 8;
   static_assert(kStageBytes >= (size_t)WAM_MAX_BATCH * 2 * 8 * 8, "host staging size");
-  if (hipHostMalloc((void**)&h->host_stage, kStageBytes, hipHostMallocDefault) != hipSuccess) {
+  if (hipHostMalloc((void**)&h->host_stage, kStageBytes,
+                    hipHostMallocMapped | hipHostMallocPortable | hipHostMallocCoherent) != hipSuccess) {
     delete h;
     return WAM_E_HIP;
   }
@@ -1084,9 +1083,7 @@ int wam_consistency_score(wam_t h, int n, const float* const* u_hat, const float
     wsum += weight[m];
   }
   if (!(wsum > 0.0)) return fail(h, WAM_E_ARG, "weights sum to zero");
-  double* sums = h->S<double>(h->ws.or_sums);
-  HIPCHK(h, launch_or_sums(n, u_hat, u, cnt, delta, sums, h->stream));
-  HIPCHK(h, hipMemcpyAsync(h->host_stage, sums, (size_t)n * kRemapChunks * 8, hipMemcpyDeviceToHost, h->stream));
+  HIPCHK(h, launch_or_sums(n, u_hat, u, cnt, delta, h->host_stage, h->stream));
   HIPCHK(h, hipStreamSynchronize(h->stream));
   double acc = 0.0;
   for (int m = 0; m < n; ++m) {

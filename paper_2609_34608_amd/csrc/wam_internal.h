@@ -215,8 +215,9 @@ struct RRGateArgs {
   const float* hs;   // h_s [M][D]
   const float* hq;   // h_q
   const float* pa;   // retained p_a
-  double* row_sums;  // [M][3]: per-row (or per-block) sums p_i p_a, p_i^2, p_a^2
+  double* row_sums;  // [M][3]: per-block sums p_i p_a, p_i^2, p_a^2
   double* result;    // [B][2][8]: Sip Sii Saa alpha cos fit pass pad
+  double* host;      // pinned host memory: when non-null, result is also stored here
   int B, T, D, Nv, Na;
   float alpha_min, alpha_max, eps, gamma_cos, gamma_fit;
 };
@@ -264,7 +265,8 @@ struct RemapArgs {
 hipError_t launch_remap(const RemapArgs& a, hipStream_t s);
 
 // Observation Rebinding: sums of ((u_hat-u)/delta)^2 per component, float64
-// run sums [n_comp][kRemapChunks] (the first reduce_chunks(n[m]) of row m)
+// run sums [n_comp][kRemapChunks] (the first reduce_chunks(n[m]) of row m) into
+// pinned host memory
 hipError_t launch_or_sums(int n_comp, const float* const* u_hat, const float* const* u,
                           const int64_t* n, const double* delta, double* sums, hipStream_t s);
 
