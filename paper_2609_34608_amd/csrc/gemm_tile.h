@@ -181,13 +181,14 @@ __device__ __forceinline__ void store_tile(const GemmArgs& a, const f32x4 (&acc)
       const int m = mb + i * 16 + lr;
       if (m >= a.M) continue;
       if constexpr (EPI == EPI_GATED_RES) {
-        // residual stream h += gate * (acc + bias): all loads of the row first;
+        // residual stream plus gate * (acc + bias): all loads of the row first;
         // with a copy target the new values are stored there as well
         const size_t off = (size_t)m * a.N + nb + lg * 4;
+        const f32x4* rrow = reinterpret_cast<const f32x4*>(a.res + off);
         f32x4* hrow = reinterpret_cast<f32x4*>(static_cast<float*>(a.out) + off);
         f32x4 hv[TN];
 #pragma unroll
-        for (int j = 0; j < TN; ++j) hv[j] = hrow[j * 4];
+        for (int j = 0; j < TN; ++j) hv[j] = rrow[j * 4];
 #pragma unroll
         for (int j = 0; j < TN; ++j) hv[j] = hv[j] + gate[j] * (acc[j][i] + bias[j]);
 #pragma unroll

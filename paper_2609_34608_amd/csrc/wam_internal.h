@@ -110,7 +110,7 @@ __device__ __forceinline__ float gelu_tanh_f(float x) {
 // ---------------------------------------------------------------- GEMM
 enum GemmEpilogue : int {
   EPI_BIAS_GELU = 1,  // out[m,n] = gelu(acc + bias[n])                 (act type)
-  EPI_GATED_RES = 2,  // h[m,n] += gate[n] * (acc + bias[n])            (float32)
+  EPI_GATED_RES = 2,  // out[m,n] = res[m,n] + gate[n] * (acc + bias[n]) (float32)
   EPI_QKV = 3,        // q,k RMS-normalised per head -> [B*H][Tpad][dh], v -> [B*H][dh][Tpad]
 };
 
@@ -130,13 +130,14 @@ struct GemmArgs {
   const void* W;     // [N][K] packed weight (act type), row stride K
   const float* bias; // [N]
   const float* gate; // [N] (EPI_GATED_RES)
-  void* out;         // [M][N] act type, or float h for EPI_GATED_RES
+  void* out;         // [M][N] act type, or float for EPI_GATED_RES (16-byte aligned)
   int M, N, K;
   int epi;
   int role;          // distinct kernel symbol per projection (0 qkv, 1 proj, 2 fc1, 3 fc2)
   QkvOut qkv;
   const int* skip;   // device flag: when non-null and set, the launch does nothing
-  float* copy;       // EPI_GATED_RES: when non-null, the updated h is also stored here ([M][N])
+  const float* res;  // EPI_GATED_RES: the residual stream [M][N]; may be out
+  float* copy;       // EPI_GATED_RES: when non-null, the result is also stored here ([M][N])
 };
 
 hipError_t launch_gemm(const GemmArgs& a, bool bf16_mode, hipStream_t s);

@@ -82,3 +82,23 @@ def test_bf16_attention_forms(dev, B, T, D, qk_norm):
     err, _ = _update_error(dev, _spec("bf16", B, T, D, 64, 2 * D, qk_norm), weight_std=0.02 if qk_norm else 0.045)
     print(f"bf16 attention B={B} T={T} D={D} qk_norm={qk_norm}: update rel err {err:.2e}")
     assert err <= BF16_UPDATE_TOL, err
+
+
+@pytest.mark.parametrize("dtype,n_layers", [("bf16", 0), ("bf16", 1), ("bf16", 2), ("fp32", 2)])
+def test_hidden_into_unaligned_output(dev, dtype, n_layers):
+    """The last layer stores into a 16-byte aligned output itself; any other
+    output receives a copy.  Same bits either way, no write past the end, and
+    repeated calls start from the same embedding."""
+    import torch
+    from paper_2609_34608_amd import runtime as R
+    spec = _spec(dtype, 2, 77, 128, 64, 512).replace(L=2)
+    m = R.WamModel(R.config_of(spec), make_weights(spec, bias_std=0.02), device=dev)
+    m.set_schedule(f32_sigmas(spec.K))
+    x, cond = to_dev(make_initial_noise(spec), dev), to_dev(make_observations(spec, 0)[0], dev)
+    n = spec.B * spec.T * spec.D
+    ref = m.hidden(1, x, cond, n_layers)
+    buf = torch.full((n + 2,), -7.0, device=dev)
+    got = m.hidden(1, x, cond, n_layers, buf[1:n + 1].view(spec.B, spec.T, spec.D))
+    assert torch.equal(ref, got) and float(buf[0]) == -7.0 and float(buf[-1]) == -7.0
+    assert torch.equal(ref, m.hidden(1, x, cond, n_layers))
+    m.close()
