@@ -695,12 +695,16 @@ __device__ __forceinline__ double run_sq_sum(const float* p, const float* q, dou
   return s;
 }
 
-// rms of (x^r - x_bar)/sigma_r per (sample, branch) over the whole branch, in
-// two launches: each branch is cut into reduce_chunks(n) runs of whole
-// 4-element groups, one block per run sums its squares (float64); then one
-// block per (sample, branch) adds the run sums in a fixed order (the same
-// bits on every call) and turns the rms into the remap coefficient
-// sigma_b0 / (sigma_r rms) (0 for a zero direction).
+// rms of (x^r - x_bar)/sigma_r per (sample, branch) over the whole branch: each
+// branch is cut into reduce_chunks(n) runs of whole 4-element groups, one
+// block per run sums its squares (float64); then the run sums are added in a
+// fixed order (the same bits on every call) and turned into the remap
+// coefficient sigma_b0 / (sigma_r rms) (0 for a zero direction).  Up to 2048
+// blocks of the remap itself (one round of the chip) every one of them does
+// that for the branches it touches while its loads are in flight, two launches
+// in all: 4 x 154 K elements 12.4 -> 9.5 us.  Beyond, repeating the sum in
+// every block costs more than the launch it saves (16 M elements: 55 us against
+// 52) and one block per (sample, branch) does it in between.
 template <bool VEC>
 __global__ __launch_bounds__(256) void remap_partial_kernel(RemapArgs a) {
   __shared__ double sh[16];
@@ -728,64 +732,68 @@ __device__ __forceinline__ double runs_sum(const double* p, int n, double* sh) {
   return block_sum_d(s, sh);
 }
 
-__global__ __launch_bounds__(256) void remap_finish_kernel(RemapArgs a) {
-  __shared__ double sh[16];
-  const int sb = blockIdx.x;
+// x = x_bar + sigma_b0 d with d = ((x^r - x_bar) / sigma_r) / rms
+__device__ __forceinline__ double remap_coef(const RemapArgs& a, int sb, double* sh) {
   const int br = sb % 2;
   const int64_t n = br == 0 ? (int64_t)a.Nv * a.Cv : (int64_t)a.Na * a.A;
   const double s = runs_sum(a.partial + (size_t)sb * kRemapChunks, reduce_chunks(n), sh);
-  if (threadIdx.x == 0) {
-    // x = x_bar + sigma_b0 d with d = ((x^r - x_bar) / sigma_r) / rms
-    const double rms = n > 0 ? sqrt(s / (double)n) : 0.0;
-    a.coef[sb] = rms > 0.0 ? (double)a.sigma_b0 / ((double)a.sigma_r * rms) : 0.0;
-  }
+  const double rms = n > 0 ? sqrt(s / (double)n) : 0.0;
+  return rms > 0.0 ? (double)a.sigma_b0 / ((double)a.sigma_r * rms) : 0.0;
+}
+
+__global__ __launch_bounds__(256) void remap_finish_kernel(RemapArgs a) {
+  __shared__ double sh[16];
+  const double c = remap_coef(a, blockIdx.x, sh);
+  if (threadIdx.x == 0) a.coef[blockIdx.x] = c;
 }
 
 // x[j] = x_bar[j+shift] + sigma_b0 d[j+shift] on mapped slots, sigma_b0 eps[j]
 // elsewhere.  Slot j of a branch of width w is mapped when j + shift < slots,
 // i.e. when the element index within the branch plus shift * w stays inside
-// the branch.  Grid (element groups, sample): with VEC each thread takes four
-// consecutive elements with 16-byte loads and stores (the host has checked
-// that the pointers, both branch lengths and both shifted offsets are
+// the branch.  Grid (runs of 256 thread items, sample): with VEC an item is four consecutive elements with 16-byte loads and stores (the host has
+// checked that the pointers, both branch lengths and both shifted offsets are
 // multiples of four floats, so a group lies in one branch and is mapped or
-// unmapped as a whole); otherwise one element per thread.  Every element is
-// computed by the same expression either way.
+// unmapped as a whole); otherwise one element.  Every element is computed by
+// the same expression either way.
 __device__ __forceinline__ float remap_value(float xb, float xr, double coef) {
   const double x = (double)xb;
   return (float)(x + ((double)xr - x) * coef);
 }
 
-template <bool VEC>
+template <bool VEC, bool FUSED>
 __global__ __launch_bounds__(256) void remap_apply_kernel(RemapArgs a) {
+  constexpr int E = VEC ? 4 : 1;
+  typedef float item __attribute__((ext_vector_type(E)));
+  __shared__ double sh[16];
   const int64_t traj = (int64_t)a.Nv * a.Cv + (int64_t)a.Na * a.A;
   const int64_t nv = (int64_t)a.Nv * a.Cv;
   const int b = blockIdx.y;
   const size_t base = (size_t)b * traj;
-  if constexpr (VEC) {
-    const int64_t i = 4 * ((int64_t)blockIdx.x * 256 + threadIdx.x);
-    if (i >= traj) return;
-    const bool video = i < nv;
-    const int64_t src = i + (video ? (int64_t)a.shift_video * a.Cv : (int64_t)a.shift_action * a.A);
-    f32x4 out;
-    if (src < (video ? nv : traj)) {
-      const f32x4 xb = *reinterpret_cast<const f32x4*>(a.x_bar + base + src);
-      const f32x4 xr = *reinterpret_cast<const f32x4*>(a.x_r + base + src);
-      const double c = a.coef[b * 2 + (video ? 0 : 1)];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) out[e] = remap_value(xb[e], xr[e], c);
-    } else {
-      out = a.sigma_b0 * *reinterpret_cast<const f32x4*>(a.noise + base + i);
-    }
-    *reinterpret_cast<f32x4*>(a.x_out + base + i) = out;
-  } else {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= traj) return;
-    const bool video = i < nv;
-    const int64_t src = i + (video ? (int64_t)a.shift_video * a.Cv : (int64_t)a.shift_action * a.A);
-    a.x_out[base + i] = src < (video ? nv : traj)
-                            ? remap_value(a.x_bar[base + src], a.x_r[base + src], a.coef[b * 2 + (video ? 0 : 1)])
-                            : a.sigma_b0 * a.noise[base + i];
+  const int64_t i0 = (int64_t)blockIdx.x * (256 * E), i = i0 + (int64_t)threadIdx.x * E;
+  const bool live = i < traj, video = i < nv;
+  const int64_t src = i + (video ? (int64_t)a.shift_video * a.Cv : (int64_t)a.shift_action * a.A);
+  const bool mapped = src < (video ? nv : traj);
+  item xb{}, xr{};
+  if (live && mapped) {
+    xb = *reinterpret_cast<const item*>(a.x_bar + base + src);
+    xr = *reinterpret_cast<const item*>(a.x_r + base + src);
+  } else if (live) {
+    xb = *reinterpret_cast<const item*>(a.noise + base + i);
   }
+  double c;
+  if constexpr (FUSED) {
+    // branches this block touches (uniform over the block)
+    const double cv = i0 < nv ? remap_coef(a, b * 2, sh) : 0.0;
+    const double ca = i0 + 256 * E > nv ? remap_coef(a, b * 2 + 1, sh) : 0.0;
+    c = video ? cv : ca;
+  } else {
+    c = a.coef[b * 2 + (video ? 0 : 1)];
+  }
+  if (!live) return;
+  item out;
+#pragma unroll
+  for (int k = 0; k < E; ++k) out[k] = mapped ? remap_value(xb[k], xr[k], c) : a.sigma_b0 * xb[k];
+  *reinterpret_cast<item*>(a.x_out + base + i) = out;
 }
 
 // ------------------------------------------------------------- Observation Rebinding
@@ -1008,11 +1016,16 @@ hipError_t launch_remap(const RemapArgs& a, hipStream_t s) {
     launch_k(remap_partial_kernel<true>, dim3(nch, a.B * 2), 256, 0, s, a);
   else
     launch_k(remap_partial_kernel<false>, dim3(nch, a.B * 2), 256, 0, s, a);
-  launch_k(remap_finish_kernel, a.B * 2, 256, 0, s, a);
-  if (apply_vec)
-    launch_k(remap_apply_kernel<true>, dim3((unsigned)((traj / 4 + 255) / 256), a.B), 256, 0, s, a);
-  else
-    launch_k(remap_apply_kernel<false>, dim3((unsigned)((traj + 255) / 256), a.B), 256, 0, s, a);
+  const int64_t items = apply_vec ? traj / 4 : traj;
+  const dim3 grid((unsigned)((items + 255) / 256), a.B);
+  if ((int64_t)grid.x * a.B <= 2048) {
+    if (apply_vec) launch_k(remap_apply_kernel<true, true>, grid, 256, 0, s, a);
+    else launch_k(remap_apply_kernel<false, true>, grid, 256, 0, s, a);
+  } else {
+    launch_k(remap_finish_kernel, a.B * 2, 256, 0, s, a);
+    if (apply_vec) launch_k(remap_apply_kernel<true, false>, grid, 256, 0, s, a);
+    else launch_k(remap_apply_kernel<false, false>, grid, 256, 0, s, a);
+  }
   return hipGetLastError();
 }
 
