@@ -261,154 +261,103 @@ __global__ __launch_bounds__(256) void ln_modulate_kernel(const float* __restric
 }
 
 // ------------------------------------------------------------- final layer + Euler
-// A block of NW waves takes NW R consecutive trajectory rows of one branch of
-// one sample, wave w the rows w R .. w R + R-1, so that all of them share the
-// branch's head weights (W^T packed [Cout][D]) and the modulation vectors,
-// which the block copies from global memory into LDS once.  A lane holds elements VEC lane + 64 VEC i ..
-// + VEC-1 of each row.  Every load that does not depend on a reduction is
-// issued up front (the rows, the modulation, the weight copy).  Each lane
-// forms partial products of its elements for R rows x 16 channels; butterfly
-// sums over the 64 lanes leave lane l < 16 R with the full dot product of row
-// l / 16, channel l % 16, which it stores as the velocity and/or applies as
-// the Euler update x += dsigma v.
+// LayerNorm, modulation and the branch's head (up to 16 channels) on the fp32
+// matrix cores, then the velocity and / or the Euler update x += dsigma v.  A
+// block of four waves takes 16 consecutive trajectory rows of one branch of
+// one sample, wave w their columns [w D/4, (w+1) D/4) in chunks of 16: lane
+// (g, r) holds columns 4g .. 4g+3 of every chunk of row r, and of head row
+// (output channel) r of W^T, which are the operands of four 16x16x4 MFMAs, so
+// neither goes through LDS.  Row sums, squared
+// deviations and the four waves' partial products meet in LDS, in wave order.
+// HBM bound on long trajectories (D = 1536, 9664 rows, 59 MB: 38 us with
+// the head in LDS and vector products, 26 us here), a chain of
+// four short phases on short ones (D = 768, 800 rows: 12.0 -> 7.2 us).
 constexpr int kFinalCout = 16;
-template <int VEC>
-using fvec = float __attribute__((ext_vector_type(VEC)));
 
-// Copies n floats (a multiple of 4) from global memory to LDS with
-// direct-to-LDS 16-byte loads, 1 KiB per instruction, runs c = first, first +
-// step, ...: lanes past the end of the last run re-read the final 16 bytes,
-// into LDS that is never read (the destination is sized in whole runs).
-__device__ __forceinline__ void copy_to_lds(const float* src, float* dst, int n, int lane, int first, int step) {
-  for (int c = first; c * 256 < n; c += step) {
-    const int e = c * 256 + 4 * lane;
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + (e < n ? e : n - 4)),
-                                     (__attribute__((address_space(3))) void*)(dst + c * 256), 16, 0, 0);
-  }
-}
-
-// D a multiple of 64 VEC, at most 64 VEC MAXC.  Each wave first requests its
-// rows (HBM; rows at or past the branch end re-read the group's first row and
-// are never stored), then the block copies the Cout x D weights (contiguous,
-// the same layout in LDS) and the modulation vectors into LDS; after a full
-// wait and the barrier each wave reads its columns of them from LDS.
-template <int VEC, int R, int MAXC, int NW>
-__global__ __launch_bounds__(NW * 64) void final_kernel(FinalArgs a) {
-  using vec = fvec<VEC>;
-  constexpr int DMAX = MAXC * 64 * VEC;  // a multiple of 256
-  __shared__ __attribute__((aligned(1024))) float wsm[kFinalCout * DMAX];
-  __shared__ __attribute__((aligned(1024))) float msc[DMAX], msh[DMAX];
+template <int MAXC>
+__global__ __launch_bounds__(256) void final_kernel(FinalArgs a) {
+  constexpr int NW = 4, R = 16;
+  __shared__ float rsum[NW][R], rsq[NW][R];
+  __shared__ float part[NW][R][kFinalCout + 1];
   const int lane = threadIdx.x % kWave, wid = threadIdx.x / kWave;
-  constexpr int RB = NW * R;  // rows per block
-  const int gv = (a.Nv + RB - 1) / RB, ga = (a.Na + RB - 1) / RB, per = gv + ga;
+  const int g = lane / 16, r = lane % 16;
+  const int gv = (a.Nv + R - 1) / R, ga = (a.Na + R - 1) / R, per = gv + ga;
   const int b = blockIdx.x / per, j = blockIdx.x % per;
   const bool video = j < gv;
-  const int t0 = (video ? j * RB : a.Nv + (j - gv) * RB) + wid * R;
+  const int t0 = video ? j * R : a.Nv + (j - gv) * R;
   const int tend = video ? a.Nv : a.Nv + a.Na;
-  const bool active = t0 < tend;  // waves past the branch end only help with the copies
-  const int nch = a.D / (kWave * VEC);
-  auto col = [&](int i) { return VEC * lane + kWave * VEC * i; };
-  vec u[R][MAXC];
-  if (active) {
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const float* hr = a.h + ((size_t)b * a.T + (t0 + r < tend ? t0 + r : t0)) * a.D;
-#pragma unroll
-      for (int i = 0; i < MAXC; ++i)
-        if (i < nch) u[r][i] = *reinterpret_cast<const vec*>(hr + col(i));
-    }
-  }
   const int cout = video ? a.Cv : a.A;
-  copy_to_lds(video ? a.wv : a.wa, wsm, cout * a.D, lane, wid, NW);
-  copy_to_lds(a.scale, msc, a.D, lane, (wid + NW - 1) % NW, NW);
-  copy_to_lds(a.shift, msh, a.D, lane, (wid + NW - 2) % NW, NW);
-  // the compiler does not track the LDS writes of those loads: wait for all
-  // of this wave's memory operations, then for every wave's
-  __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();
-  if (!active) return;
-
-  float mean[R], rstd[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    float s = 0.f;
-#pragma unroll
-    for (int i = 0; i < MAXC; ++i)
-      if (i < nch)
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) s += u[r][i][e];
-    mean[r] = wave_sum(s) / (float)a.D;
-  }
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    float q = 0.f;
-#pragma unroll
-    for (int i = 0; i < MAXC; ++i)
-      if (i < nch)
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) {
-          const float dv = u[r][i][e] - mean[r];
-          q += dv * dv;
-        }
-    rstd[r] = rsqrtf(wave_sum(q) / (float)a.D + a.eps);
-  }
+  const int nc = a.D / 64;  // chunks of 16 columns per wave
+  const int c0 = wid * (a.D / 4) + 4 * g;
+  // rows past the branch and channels past the head read the last one of it;
+  // what they give is never stored
+  const float* hr = a.h + ((size_t)b * a.T + min(t0 + r, tend - 1)) * a.D + c0;
+  const float* wr = (video ? a.wv : a.wa) + (size_t)min(r, cout - 1) * a.D + c0;
+  // modulation and head: ahead of the reductions too where the registers
+  // allow it, else (two waves per SIMD matter more) from L2 as they are used
+  constexpr bool kAhead = MAXC <= 12;
+  constexpr int MW = kAhead ? MAXC : 1;
+  f32x4 u[MAXC], w[MW], sc[MW], sh[MW];
+  auto load_mod = [&](int i, int at) {
+    sc[at] = *reinterpret_cast<const f32x4*>(a.scale + c0 + 16 * i);
+    sh[at] = *reinterpret_cast<const f32x4*>(a.shift + c0 + 16 * i);
+    w[at] = *reinterpret_cast<const f32x4*>(wr + 16 * i);
+  };
 #pragma unroll
   for (int i = 0; i < MAXC; ++i)
-    if (i < nch) {
-      const vec sc = *reinterpret_cast<const vec*>(msc + col(i));
-      const vec sh = *reinterpret_cast<const vec*>(msh + col(i));
+    if (i < nc) u[i] = *reinterpret_cast<const f32x4*>(hr + 16 * i);
+  if constexpr (kAhead) {
 #pragma unroll
-      for (int r = 0; r < R; ++r) u[r][i] = (u[r][i] - mean[r]) * rstd[r] * (1.0f + sc) + sh;
-    }
-  constexpr int NV = R * kFinalCout;  // partial sums per lane, index r * 16 + o
-  float v[NV];
-#pragma unroll
-  for (int k = 0; k < NV; ++k) v[k] = 0.f;
-#pragma unroll
-  for (int i = 0; i < MAXC; ++i) {
-    if (i < nch) {
-      vec w[kFinalCout];
-#pragma unroll
-      for (int o = 0; o < kFinalCout; ++o)
-        w[o] = o < cout ? *reinterpret_cast<const vec*>(wsm + o * a.D + col(i)) : vec(0.f);
-#pragma unroll
-      for (int r = 0; r < R; ++r)
-#pragma unroll
-        for (int o = 0; o < kFinalCout; ++o) {
-          const vec p = u[r][i] * w[o];
-#pragma unroll
-          for (int e = 0; e < VEC; ++e) v[r * kFinalCout + o] += p[e];
-        }
-    }
+    for (int i = 0; i < MAXC; ++i)
+      if (i < nc) load_mod(i, i);
   }
-  // lane bits above NV: plain butterfly sums; then a reduce-scatter, where
-  // after the step over lane bit s, v[k] (k < s) holds the partial sum of
-  // index k + (lane & s) + the bits already consumed.  Lane l ends with the
-  // full sum of index l % NV.
+  __builtin_amdgcn_sched_barrier(0);  // keep these loads ahead of the reductions
+  // sum over the columns of row r: lane, the row's four lanes, the four waves
+  auto row_sum = [&](float v, float (*buf)[R]) {
+    v += __shfl_xor(v, 16, 64);
+    v += __shfl_xor(v, 32, 64);
+    if (g == 0) buf[wid][r] = v;
+    __syncthreads();
+    return (buf[0][r] + buf[1][r]) + (buf[2][r] + buf[3][r]);
+  };
+  float s = 0.f;
 #pragma unroll
-  for (int s = kWave / 2; s >= NV; s >>= 1)
+  for (int i = 0; i < MAXC; ++i)
+    if (i < nc) s += (u[i].x + u[i].y) + (u[i].z + u[i].w);
+  const float mean = row_sum(s, rsum) / (float)a.D;
+  float q = 0.f;
 #pragma unroll
-    for (int k = 0; k < NV; ++k) v[k] += __shfl_xor(v[k], s, 64);
-#pragma unroll
-  for (int s = NV / 2; s >= 1; s >>= 1) {
-    const bool hi = (lane & s) != 0;
-#pragma unroll
-    for (int k = 0; k < s; ++k) {
-      const float keep = hi ? v[k + s] : v[k];
-      const float send = hi ? v[k] : v[k + s];
-      v[k] = keep + __shfl_xor(send, s, 64);
+  for (int i = 0; i < MAXC; ++i)
+    if (i < nc) {
+      u[i] -= mean;
+      q += (u[i].x * u[i].x + u[i].y * u[i].y) + (u[i].z * u[i].z + u[i].w * u[i].w);
     }
-  }
-  const int r = lane / kFinalCout, o = lane % kFinalCout, t = t0 + r;
-  if (lane >= NV || t >= tend || o >= cout) return;
-  const float vel = v[0] + (video ? a.bv : a.ba)[o];
+  const float rstd = rsqrtf(row_sum(q, rsq) / (float)a.D + a.eps);
+  // out^T = W^T u^T: lane (g, r) ends with channels 4g .. 4g+3 of row r
+  f32x4 acc[4] = {};  // one accumulator per k: shorter sums and no MFMA waiting for the last
+#pragma unroll
+  for (int i = 0; i < MAXC; ++i)
+    if (i < nc) {
+      const int at = kAhead ? i : 0;
+      if constexpr (!kAhead) load_mod(i, 0);
+      const f32x4 m = u[i] * rstd * (1.0f + sc[at]) + sh[at];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) acc[k] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[at][k], m[k], acc[k], 0, 0, 0);
+    }
+  acc[0] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) part[wid][r][4 * g + k] = acc[0][k];
+  __syncthreads();
+  const int row = threadIdx.x / kFinalCout, o = threadIdx.x % kFinalCout, t = t0 + row;
+  if (t >= tend || o >= cout) return;
+  const float vel = ((part[0][row][o] + part[1][row][o]) + (part[2][row][o] + part[3][row][o])) +
+                    (video ? a.bv : a.ba)[o];
   const int traj = a.Nv * a.Cv + a.Na * a.A;
   const size_t idx = (size_t)b * traj + (video ? (size_t)t * a.Cv + o
                                                : (size_t)a.Nv * a.Cv + (size_t)(t - a.Nv) * a.A + o);
   if (a.v_out) a.v_out[idx] = vel;
   if (a.x) a.x[idx] += a.dsigma * vel;
 }
-
 
 // ------------------------------------------------------------- Residual Rescaling
 // alpha (Eq. crr-alpha), cos and relative fit error (Eq. crr-gate) of one
@@ -904,41 +853,18 @@ hipError_t launch_ln_modulate(const float* h, const float* shift, const float* s
   return hipGetLastError();
 }
 
-template <int VEC, int R, int MAXC, int NW = 8>
-void launch_final_t(const FinalArgs& a, hipStream_t s) {
-  constexpr int RB = NW * R;
-  const int blocks = a.B * ((a.Nv + RB - 1) / RB + (a.Na + RB - 1) / RB);
-  if (blocks > 0) launch_k(final_kernel<VEC, R, MAXC, NW>, blocks, NW * 64, 0, s, a);
-}
-
 hipError_t launch_final(const FinalArgs& a, hipStream_t s) {
   if (a.D % kWave || a.D > 2048 || a.Cv > kFinalCout || a.A > kFinalCout) return hipErrorInvalidValue;
-  // the widest column vector D allows; the smallest LDS copy that holds the
-  // weights (48 KB at D <= 768, so that several blocks share a CU); four rows
-  // per wave share each weight read (two where the rows' registers would not
-  // fit), or one row per wave for short trajectories (under 4096 rows: the
-  // small model's 800 rows as 100 blocks of 8)
-  const bool many = (long)a.B * (a.Nv + a.Na) >= 4096;
-  if (a.D % 256 == 0) {
-    if (a.D <= 768)
-      many ? launch_final_t<4, 4, 3>(a, s) : launch_final_t<4, 1, 3>(a, s);
-    else if (a.D <= 1024)
-      many ? launch_final_t<4, 4, 4>(a, s) : launch_final_t<4, 1, 4>(a, s);
-    else if (a.D <= 1536)
-      many ? launch_final_t<4, 4, 6>(a, s) : launch_final_t<4, 1, 6>(a, s);
-    else
-      launch_final_t<4, 2, 8>(a, s);
-  } else if (a.D % 128 == 0) {
-    if (a.D <= 1024)
-      many ? launch_final_t<2, 4, 8>(a, s) : launch_final_t<2, 1, 8>(a, s);
-    else
-      launch_final_t<2, 2, 16>(a, s);
-  } else {
-    if (a.D <= 1024)
-      many ? launch_final_t<1, 4, 16>(a, s) : launch_final_t<1, 1, 16>(a, s);
-    else
-      launch_final_t<1, 2, 32>(a, s);
-  }
+  const int blocks = a.B * ((a.Nv + 15) / 16 + (a.Na + 15) / 16);
+  if (blocks == 0) return hipSuccess;
+  // registers for the chunks D needs
+  const int nc = a.D / 64;
+  if (nc <= 4) launch_k(final_kernel<4>, blocks, 256, 0, s, a);
+  else if (nc <= 8) launch_k(final_kernel<8>, blocks, 256, 0, s, a);
+  else if (nc <= 12) launch_k(final_kernel<12>, blocks, 256, 0, s, a);
+  else if (nc <= 16) launch_k(final_kernel<16>, blocks, 256, 0, s, a);
+  else if (nc <= 24) launch_k(final_kernel<24>, blocks, 256, 0, s, a);
+  else launch_k(final_kernel<32>, blocks, 256, 0, s, a);
   return hipGetLastError();
 }
 
