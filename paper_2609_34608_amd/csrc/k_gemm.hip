@@ -11,7 +11,7 @@ using gemm::launch_tile;
 using gemm::launch_tile_f32;
 
 // ---------------------------------------------------------------- configs
-// Tile shapes of the bf16 kernel and what a tile costs.  A CU that holds c
+// Tile shapes and what a tile costs.  A CU that holds c
 // blocks at once (c <= occ) finishes them in about K / 64 * per[c-1] +
 // fix[c-1] us; the constants are least-squares fits to timings of every
 // configuration at the four projections of 57 model sizes (64 to 12000 rows,
@@ -24,7 +24,7 @@ using gemm::launch_tile_f32;
 struct TileCfg {
   int bm, bn, wgm, wgn, st, bk;  // rows x columns, waves (rows x columns), LDS stages, K per stage
   int occ;
-  float per[3], fix[3];
+  float per[4], fix[4];
 };
 constexpr TileCfg kCfgs[] = {
     {256, 256, 2, 4, 2, 64, 1, {1.38f}, {7.85f}},
@@ -49,10 +49,41 @@ hipError_t launch_c(const GemmArgs& a, hipStream_t s) {
   return launch_tile<t.bm, t.bn, t.wgm, t.wgn, t.st, t.bk>(a, s);
 }
 
+// float32 operands: the fp32 matrix rate (157 TFLOP/s, a sixteenth of bf16)
+// leaves loads and LDS far from their limits at any tile, so the tile has to
+// spread the work evenly; large ones run their MFMAs with fewer gaps (96x128
+// at 80% of the rate, 32x32 at 60%).  Same cost form, fitted at 39 sizes (64
+// to 6000 rows, D 64 to 1024; standard deviation 3-8%): the choice is 0.5%
+// off the fastest on average.  M = 864, D = 768 on the vector pipe before:
+// QKV 65 -> 31 us, attention output 58 -> 15, MLP-up 79 -> 43, MLP-down 214 ->
+// 48.
+constexpr TileCfg kF32Cfgs[] = {
+    {128, 128, 2, 2, 2, 32, 1, {4.01f}, {4.4f}},
+    {96, 128, 2, 2, 3, 32, 1, {3.04f}, {4.3f}},
+    {64, 128, 2, 2, 3, 32, 2, {2.11f, 4.34f}, {4.0f, 6.4f}},
+    {64, 64, 2, 4, 3, 32, 3, {1.11f, 2.13f, 3.37f}, {3.0f, 4.8f, 1.5f}},
+    {32, 32, 2, 2, 4, 32, 3, {0.42f, 0.65f, 0.92f}, {2.5f, 2.9f, 1.6f}},
+    {16, 64, 1, 1, 4, 32, 4, {1.10f, 1.14f, 1.21f, 1.27f}, {3.1f, 3.4f, 3.6f, 2.5f}},
+};
+constexpr int kNumF32Cfgs = sizeof(kF32Cfgs) / sizeof(kF32Cfgs[0]);
+
+template <int C>
+hipError_t launch_f32(const GemmArgs& a, hipStream_t s) {
+  constexpr TileCfg t = kF32Cfgs[C];
+  return launch_tile_f32<t.bm, t.bn, t.wgm, t.wgn, t.st, t.bk>(a, s);
+}
+
 template <int... C>
 hipError_t launch_any(const GemmArgs& a, int cfg, hipStream_t s, std::integer_sequence<int, C...>) {
   hipError_t e = hipErrorInvalidValue;
   ((cfg == C ? (void)(e = launch_c<C>(a, s)) : (void)0), ...);
+  return e;
+}
+
+template <int... C>
+hipError_t launch_any_f32(const GemmArgs& a, int cfg, hipStream_t s, std::integer_sequence<int, C...>) {
+  hipError_t e = hipErrorInvalidValue;
+  ((cfg == C ? (void)(e = launch_f32<C>(a, s)) : (void)0), ...);
   return e;
 }
 
@@ -66,17 +97,18 @@ double tile_cost(const TileCfg& t, int M, int N, int K) {
   return c;
 }
 
-// Configuration of the smallest cost.  Over those sizes its choice is 1.3%
+// Configuration of the smallest cost.  Over the bf16 sizes its choice is 1.3%
 // slower than the fastest configuration on average (21% at worst, on a 5 us
 // launch); the fixed rules it replaced, with tiles that had to divide N, were
 // 22% slower on average, e.g. N = 1216, M = 5754: 41 -> 26 us (K = 1216) and
 // 122 -> 74 us (K = 4864).
-int plan_gemm(int M, int N, int K, int epi) {
+template <int NC>
+int plan_gemm(const TileCfg (&cfgs)[NC], int M, int N, int K, int epi) {
   int best = -1;
   double bc = 0.0;
-  for (int c = 0; c < kNumCfgs; ++c) {
-    const TileCfg& t = kCfgs[c];
-    // the QKV epilogue needs whole heads (64 columns) per wave
+  for (int c = 0; c < NC; ++c) {
+    const TileCfg& t = cfgs[c];
+    // the QKV epilogue needs whole heads (up to 64 columns) per wave
     if (K % t.bk || (epi == EPI_QKV && (t.bn / t.wgn) % 64)) continue;
     const double v = tile_cost(t, M, N, K);
     if (best < 0 || v < bc) best = c, bc = v;
@@ -84,39 +116,15 @@ int plan_gemm(int M, int N, int K, int epi) {
   return best;
 }
 
-// ---------------------------------------------------------------- fp32
-// The fp32 matrix rate (157 TFLOP/s, a sixteenth of bf16) leaves loads and
-// LDS far from their limits at any tile, so the tile only has to spread the
-// work evenly: 64x64 where the last wave of blocks costs less than the better
-// balance of 32-row or 32x32 tiles (counted as the tile area of the busiest
-// CU; the small tiles pay ~10% for their shorter MFMA runs).  One wave column
-// of 64 where a wave has to own whole heads (QKV epilogue).
-// Small model, M = 864, against 64x64 tiles on the vector pipe (15-20
-// TFLOP/s): QKV 65 -> 36 us, attention output 58 -> 16, MLP-up 79 -> 52,
-// MLP-down 214 -> 52.
-hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t s) {
-  if (a.K % 32 || a.N % 64) return hipErrorInvalidValue;
-  auto cost = [&](int bm, int bn, double per) {
-    const long blocks = (long)((a.M + bm - 1) / bm) * (a.N / bn);
-    return (double)((blocks + 255) / 256) * bm * bn * per;
-  };
-  const double c64 = cost(64, 64, 1.0);
-  if (a.epi == EPI_QKV)
-    return cost(32, 64, 1.05) < c64 ? launch_tile_f32<32, 64, 2, 1, 4, 32>(a, s)
-                                    : launch_tile_f32<64, 64, 4, 1, 3, 32>(a, s);
-  return cost(32, 32, 1.1) < c64 ? launch_tile_f32<32, 32, 2, 2, 4, 32>(a, s)
-                                 : launch_tile_f32<64, 64, 2, 2, 3, 32>(a, s);
-}
-
 }  // namespace
 
 hipError_t launch_gemm(const GemmArgs& a, bool bf16_mode, hipStream_t s) {
   if (a.M <= 0) return hipSuccess;
-  if (bf16_mode) {
-    if (a.N % 64) return hipErrorInvalidValue;  // ragged column tiles end on a wave's columns
-    return launch_any(a, plan_gemm(a.M, a.N, a.K, a.epi), s, std::make_integer_sequence<int, kNumCfgs>{});
-  }
-  return launch_gemm_f32(a, s);
+  if (a.N % 64) return hipErrorInvalidValue;  // ragged column tiles end on a wave's columns
+  if (bf16_mode)
+    return launch_any(a, plan_gemm(kCfgs, a.M, a.N, a.K, a.epi), s, std::make_integer_sequence<int, kNumCfgs>{});
+  return launch_any_f32(a, plan_gemm(kF32Cfgs, a.M, a.N, a.K, a.epi), s,
+                        std::make_integer_sequence<int, kNumF32Cfgs>{});
 }
 
 }  // namespace wam
