@@ -246,7 +246,7 @@ __global__ __launch_bounds__(256) void ln_modulate_kernel(const float* __restric
     const float t = (a * a + b * b) + (c * c + d * d);
     q += i < N4 - 1 || live ? t : 0.f;
   }
-  const float rstd = rsqrtf(wave_sum(q) / (float)D + eps);
+  const float rstd = rsqrt_newton(wave_sum(q) / (float)D + eps);
   TOut* ur = u + (size_t)row * D;
 #pragma unroll
   for (int i = 0; i < N4; ++i) {
@@ -332,9 +332,10 @@ __global__ __launch_bounds__(256) void final_kernel(FinalArgs a) {
       u[i] -= mean;
       q += (u[i].x * u[i].x + u[i].y * u[i].y) + (u[i].z * u[i].z + u[i].w * u[i].w);
     }
-  const float rstd = rsqrtf(row_sum(q, rsq) / (float)a.D + a.eps);
+  const float rstd = rsqrt_newton(row_sum(q, rsq) / (float)a.D + a.eps);
   // out^T = W^T u^T: lane (g, r) ends with channels 4g .. 4g+3 of row r
-  f32x4 acc[4] = {};  // one accumulator per k: shorter sums and no MFMA waiting for the last
+  // several accumulators: shorter sums, and no MFMA waits for the last
+  f32x4 acc[2][4] = {};
 #pragma unroll
   for (int i = 0; i < MAXC; ++i)
     if (i < nc) {
@@ -342,11 +343,12 @@ __global__ __launch_bounds__(256) void final_kernel(FinalArgs a) {
       if constexpr (!kAhead) load_mod(i, 0);
       const f32x4 m = u[i] * rstd * (1.0f + sc[at]) + sh[at];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) acc[k] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[at][k], m[k], acc[k], 0, 0, 0);
+      for (int k = 0; k < 4; ++k) acc[i % 2][k] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[at][k], m[k], acc[i % 2][k], 0, 0, 0);
     }
-  acc[0] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+  const f32x4 sum = ((acc[0][0] + acc[1][0]) + (acc[0][1] + acc[1][1])) +
+                    ((acc[0][2] + acc[1][2]) + (acc[0][3] + acc[1][3]));
 #pragma unroll
-  for (int k = 0; k < 4; ++k) part[wid][r][4 * g + k] = acc[0][k];
+  for (int k = 0; k < 4; ++k) part[wid][r][4 * g + k] = sum[k];
   __syncthreads();
   const int row = threadIdx.x / kFinalCout, o = threadIdx.x % kFinalCout, t = t0 + row;
   if (t >= tend || o >= cout) return;

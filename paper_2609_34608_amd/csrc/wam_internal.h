@@ -95,6 +95,14 @@ __device__ __forceinline__ float wave_max(float v) {
   return v;
 }
 
+// 1 / sqrt(x) for the normalisations: the hardware estimate (1 ulp) and one
+// Newton step.  Its error is common to a whole row, so it does not average
+// out as the rounding of the row's elements does.
+__device__ __forceinline__ float rsqrt_newton(float x) {
+  const float r = __builtin_amdgcn_rsqf(x);
+  return fmaf(0.5f * r, fmaf(-x * r, r, 1.0f), r);
+}
+
 // GELU, tanh form: x/2 (1 + tanh(u)), u = sqrt(2/pi)(x + 0.044715 x^3),
 // evaluated as x * sigmoid(2u) = x / (1 + 2^(-2u log2 e)) (the same function)
 // with the hardware exp2 and reciprocal (v_exp_f32, v_rcp_f32: about 1 ulp)
