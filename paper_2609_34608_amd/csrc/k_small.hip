@@ -742,28 +742,29 @@ __global__ __launch_bounds__(256) void remap_apply_kernel(RemapArgs a) {
   const size_t base = (size_t)b * traj;
   const int64_t i0 = (int64_t)blockIdx.x * (256 * E), i = i0 + (int64_t)threadIdx.x * E;
   const bool live = i < traj, video = i < nv;
+  if (!FUSED && !live) return;
   const int64_t src = i + (video ? (int64_t)a.shift_video * a.Cv : (int64_t)a.shift_action * a.A);
   const bool mapped = src < (video ? nv : traj);
   item xb{}, xr{};
   if (live && mapped) {
     xb = *reinterpret_cast<const item*>(a.x_bar + base + src);
     xr = *reinterpret_cast<const item*>(a.x_r + base + src);
-  } else if (live) {
-    xb = *reinterpret_cast<const item*>(a.noise + base + i);
   }
-  double c;
+  double cv = 0.0, ca = 0.0;
   if constexpr (FUSED) {
     // branches this block touches (uniform over the block)
-    const double cv = i0 < nv ? remap_coef(a, b * 2, sh) : 0.0;
-    const double ca = i0 + 256 * E > nv ? remap_coef(a, b * 2 + 1, sh) : 0.0;
-    c = video ? cv : ca;
-  } else {
-    c = a.coef[b * 2 + (video ? 0 : 1)];
+    if (i0 < nv) cv = remap_coef(a, b * 2, sh);
+    if (i0 + 256 * E > nv) ca = remap_coef(a, b * 2 + 1, sh);
+    if (!live) return;
   }
-  if (!live) return;
   item out;
+  if (mapped) {
+    const double c = FUSED ? (video ? cv : ca) : a.coef[b * 2 + (video ? 0 : 1)];
 #pragma unroll
-  for (int k = 0; k < E; ++k) out[k] = mapped ? remap_value(xb[k], xr[k], c) : a.sigma_b0 * xb[k];
+    for (int k = 0; k < E; ++k) out[k] = remap_value(xb[k], xr[k], c);
+  } else {
+    out = a.sigma_b0 * *reinterpret_cast<const item*>(a.noise + base + i);
+  }
   *reinterpret_cast<item*>(a.x_out + base + i) = out;
 }
 

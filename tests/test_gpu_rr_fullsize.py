@@ -1,5 +1,5 @@
 """Residual Rescaling at the mid (B = 4, T = 2306) and large (T = 10176)
-shapes, and on a short sequence whose projections split K over blocks,
+shapes, and on a short sequence (small GEMM tiles),
 against the oracle, teacher-forced on the device's own hidden states.
 
 Step 0 runs with the layer state empty: every layer is computed and the
@@ -46,9 +46,8 @@ def _say(name, t0, what):
 
 def _model(name, dev):
     """The workload's cached model, or for "small_short" the small model on
-    a 64-token sequence with two samples: its 128 rows make the attention
-    output and MLP-down projections split K over blocks, so the head's h_q
-    is stored by the split reduce pass rather than the tile epilogue."""
+    a 64-token sequence with two samples: its 128 rows take the smallest
+    GEMM tiles, whose epilogue stores the head's h_q."""
     if name != "small_short":
         return model_for(name, dev)
     from paper_2609_34608_amd import runtime as R
