@@ -140,84 +140,64 @@ __global__ void embed_kernel(EmbedArgs a) {
   }
 }
 
-// Vectorised form: a block takes up to R <= kEmbedMaxRows consecutive rows of
-// one branch (video, action or observation tokens) of one sample; thread i
-// owns columns 4i..4i+3 (D / 4 threads) and keeps the up to kEmbedC weight rows
-// there in registers (clamped to the branch's channel count against
-// zero-padded token values).  The rows go by in groups of S: the position
-// embedding of the next group is requested before this one's sums, so R is
-// free to grow until the weight reads from L2 (64 KB a block at D = 1024) stop
-// mattering, without holding R rows in registers.
-// HBM bound (4 B written and, once per sample, 4 B of position embedding read
-// per element); against rows of up to 8 held in registers: 1 x 10176 rows,
-// D = 1536 33 -> 22 us, 4 x 2306, D = 1024 17.5 -> 14.5, 2 x 2877, D = 1216
-// 16.7 -> 11.4.
+// Vectorised form: a block takes up to R consecutive rows of one branch
+// (video, action or observation tokens) of one sample, so that the branch's
+// weight rows are read once for all of them (with one row per block the
+// weight reads from L2 outweighed the HBM traffic of long sequences: 66 ->
+// 33 us at T = 10176 with R = 8); thread i owns columns 4i..4i+3 (D / 4
+// threads).  Every load a thread needs (bias, the up to kEmbedC weight rows,
+// clamped to the branch's channel count against zero-padded token values,
+// and the position-embedding rows) is issued before the sums.
 constexpr int kEmbedC = 16;
-constexpr int kEmbedMaxRows = 16;
 __host__ __device__ inline int embed_blocks_per_sample(int Nv, int Na, int No, int R) {
   return (Nv + R - 1) / R + (Na + R - 1) / R + (No + R - 1) / R;
 }
-template <int S>
-__global__ __launch_bounds__(512) void embed_v4_kernel(EmbedArgs a, int R) {
+template <int R>
+__global__ __launch_bounds__(512) void embed_v4_kernel(EmbedArgs a) {
+  constexpr int kEmbedRows = R;
   const int per = embed_blocks_per_sample(a.Nv, a.Na, a.No, R);
   const int b = blockIdx.x / per, j = blockIdx.x % per;
-  const int gv = (a.Nv + R - 1) / R, ga = (a.Na + R - 1) / R;
+  const int gv = (a.Nv + kEmbedRows - 1) / kEmbedRows, ga = (a.Na + kEmbedRows - 1) / kEmbedRows;
   const float* w;
   const float* bias;
   const float* src;  // token values of the block's first row
   int c, t0, n;      // channels, first row (within the sample), rows of this block
   const int traj = a.Nv * a.Cv + a.Na * a.A;
   if (j < gv) {
-    t0 = j * R, n = min(R, a.Nv - t0), c = a.Cv, w = a.wv, bias = a.bv;
+    t0 = j * kEmbedRows, n = min(kEmbedRows, a.Nv - t0), c = a.Cv, w = a.wv, bias = a.bv;
     src = a.x + (size_t)b * traj + (size_t)t0 * a.Cv;
   } else if (j < gv + ga) {
-    const int i0 = (j - gv) * R;
-    t0 = a.Nv + i0, n = min(R, a.Na - i0), c = a.A, w = a.wa, bias = a.ba;
+    const int i0 = (j - gv) * kEmbedRows;
+    t0 = a.Nv + i0, n = min(kEmbedRows, a.Na - i0), c = a.A, w = a.wa, bias = a.ba;
     src = a.x + (size_t)b * traj + (size_t)a.Nv * a.Cv + (size_t)i0 * a.A;
   } else {
-    const int i0 = (j - gv - ga) * R;
-    t0 = a.Nv + a.Na + i0, n = min(R, a.No - i0), c = a.Co, w = a.wo, bias = a.bo;
+    const int i0 = (j - gv - ga) * kEmbedRows;
+    t0 = a.Nv + a.Na + i0, n = min(kEmbedRows, a.No - i0), c = a.Co, w = a.wo, bias = a.bo;
     src = a.cond + ((size_t)b * a.No + i0) * a.Co;
   }
-  __shared__ __attribute__((aligned(16))) float tok[kEmbedMaxRows][kEmbedC];
+  __shared__ float tok[kEmbedRows][kEmbedC];
+  for (int i = threadIdx.x; i < kEmbedRows * kEmbedC; i += blockDim.x) {
+    const int r = i / kEmbedC, ch = i % kEmbedC;
+    tok[r][ch] = r < n && ch < c ? src[(size_t)r * c + ch] : 0.f;
+  }
   const int col = threadIdx.x * 4;
   const bool live = col < a.D;
   const int cc = live ? col : 0;
-  const float* pe = a.pe + (size_t)t0 * a.D + cc;
-  float* h = a.h + ((size_t)b * a.T + t0) * a.D + cc;
-  f32x4 w4[kEmbedC], p4[S];
+  const f32x4 b4 = *reinterpret_cast<const f32x4*>(bias + cc);
+  f32x4 w4[kEmbedC], p4[kEmbedRows];
 #pragma unroll
   for (int k = 0; k < kEmbedC; ++k) w4[k] = *reinterpret_cast<const f32x4*>(w + (size_t)min(k, c - 1) * a.D + cc);
-  const f32x4 b4 = *reinterpret_cast<const f32x4*>(bias + cc);
 #pragma unroll
-  for (int r = 0; r < S; ++r) p4[r] = *reinterpret_cast<const f32x4*>(pe + (size_t)min(r, n - 1) * a.D);
-  for (int i = threadIdx.x; i < n * kEmbedC; i += blockDim.x) {
-    const int r = i / kEmbedC, ch = i % kEmbedC;
-    tok[r][ch] = ch < c ? src[(size_t)r * c + ch] : 0.f;
-  }
+  for (int r = 0; r < kEmbedRows; ++r)
+    p4[r] = *reinterpret_cast<const f32x4*>(a.pe + (size_t)(t0 + min(r, n - 1)) * a.D + cc);
   __syncthreads();
-  for (int r0 = 0; r0 < n; r0 += S) {
-    f32x4 pn[S] = {};
-    if (r0 + S < n) {
 #pragma unroll
-      for (int r = 0; r < S; ++r) pn[r] = *reinterpret_cast<const f32x4*>(pe + (size_t)min(r0 + S + r, n - 1) * a.D);
-    }
-    __builtin_amdgcn_sched_barrier(0);
+  for (int r = 0; r < kEmbedRows; ++r) {
+    if (r >= n) break;
+    f32x4 acc = b4;
 #pragma unroll
-    for (int r = 0; r < S; ++r) {
-      if (r0 + r >= n) break;
-      const f32x4* t4 = reinterpret_cast<const f32x4*>(tok[r0 + r]);
-      f32x4 acc = b4;
-#pragma unroll
-      for (int k4 = 0; k4 < kEmbedC / 4; ++k4) {
-        const f32x4 t = t4[k4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) acc += t[k] * w4[4 * k4 + k];
-      }
-      if (live) *reinterpret_cast<f32x4*>(h + (size_t)(r0 + r) * a.D) = acc + p4[r];
-    }
-#pragma unroll
-    for (int r = 0; r < S; ++r) p4[r] = pn[r];
+    for (int k = 0; k < kEmbedC; ++k) acc += tok[r][k] * w4[k];
+    if (live) *reinterpret_cast<f32x4*>(a.h + ((size_t)b * a.T + t0 + r) * a.D + col) = acc + p4[r];
   }
 }
 
@@ -828,20 +808,17 @@ hipError_t launch_embed(const EmbedArgs& a, hipStream_t s) {
   const bool chans = (a.Nv == 0 || a.Cv >= 1) && (a.Na == 0 || a.A >= 1) && (a.No == 0 || a.Co >= 1);
   if (a.D % 4 == 0 && a.D <= 2048 && a.Cv <= kEmbedC && a.A <= kEmbedC && a.Co <= kEmbedC && chans) {
     const int threads = (a.D / 4 + kWave - 1) / kWave * kWave;
-    // rows per block: a block costs its rows plus about six for its start and
-    // weights, a CU takes ceil(blocks / 256) of them, and about eight waves per
-    // CU are needed to keep its memory busy (fits the timings of 1 to 32 rows
-    // per block at ten sizes within 15%)
-    int R = 1;
-    double best = 0.0;
-    for (const int r : {1, 2, 4, 8, 12, 16}) {
-      const int blocks = a.B * embed_blocks_per_sample(a.Nv, a.Na, a.No, r);
-      const double v = std::max<double>((blocks + 255) / 256, 8.0 * kWave / threads) * (r + 6);
-      if (r == 1 || v < best) R = r, best = v;
-    }
-    const int blocks = a.B * embed_blocks_per_sample(a.Nv, a.Na, a.No, R);
-    if (R < 4) launch_k(embed_v4_kernel<2>, blocks, threads, 0, s, a, R);
-    else launch_k(embed_v4_kernel<4>, blocks, threads, 0, s, a, R);
+    // rows per block: share the weight reads where the grid stays above
+    // ~1000 blocks, one row per block for short sequences (latency)
+    const long rows = (long)a.B * a.T;
+    if (rows >= 8192)
+      launch_k(embed_v4_kernel<8>, a.B * embed_blocks_per_sample(a.Nv, a.Na, a.No, 8), threads, 0, s, a);
+    else if (rows >= 4096)
+      launch_k(embed_v4_kernel<4>, a.B * embed_blocks_per_sample(a.Nv, a.Na, a.No, 4), threads, 0, s, a);
+    else if (rows >= 2048)
+      launch_k(embed_v4_kernel<2>, a.B * embed_blocks_per_sample(a.Nv, a.Na, a.No, 2), threads, 0, s, a);
+    else
+      launch_k(embed_v4_kernel<1>, a.B * embed_blocks_per_sample(a.Nv, a.Na, a.No, 1), threads, 0, s, a);
   } else {
     launch_k(embed_kernel, a.B * a.T, 256, 0, s, a);
   }
