@@ -97,10 +97,13 @@ __device__ __forceinline__ float wave_max(float v) {
 
 // 1 / sqrt(x) for the normalisations: the hardware estimate (1 ulp) and one
 // Newton step.  Its error is common to a whole row, so it does not average
-// out as the rounding of the row's elements does.
+// out as the rounding of the row's elements does.  A sum of squares past the
+// float32 range (x = inf) gives 0, as the estimate does: the step itself would
+// be inf * 0.
 __device__ __forceinline__ float rsqrt_newton(float x) {
-  const float r = __builtin_amdgcn_rsqf(x);
-  return fmaf(0.5f * r, fmaf(-x * r, r, 1.0f), r);
+  const float r = rsqrtf(x);
+  const float n = fmaf(0.5f * r, fmaf(-x * r, r, 1.0f), r);
+  return r > 0.f && r < INFINITY ? n : r;
 }
 
 // GELU, tanh form: x/2 (1 + tanh(u)), u = sqrt(2/pi)(x + 0.044715 x^3),

@@ -102,3 +102,44 @@ def test_hidden_into_unaligned_output(dev, dtype, n_layers):
     assert torch.equal(ref, got) and float(buf[0]) == -7.0 and float(buf[-1]) == -7.0
     assert torch.equal(ref, m.hidden(1, x, cond, n_layers))
     m.close()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+def test_overflowing_rows(dev, dtype, monkeypatch):
+    """Rows whose sum of squares overflows float32 have scale zero: LayerNorm
+    leaves the shift of its modulation, and q and k of such a head are zero
+    (its softmax uniform), in the layer and in the final layer.  The trajectory
+    rows here are of order 1e20 (their update is lost in h's rounding), the
+    observation rows ordinary, and one head has a q bias of 1e21."""
+    from paper_2609_34608_amd import runtime as R
+    spec = _spec(dtype, 2, 77, 128, 64, 256)
+    W = make_weights(spec, bias_std=0.02, gain_std=0.1, weight_std=0.05)
+    W["l0.qkv_b"][:64] = 1e21
+    m = R.WamModel(R.config_of(spec), W, device=dev)
+    sig = f32_sigmas(spec.K)
+    m.set_schedule(sig)
+    x, cond = to_dev(make_initial_noise(spec) * 1e21, dev), to_dev(make_observations(spec, 0)[0], dev)
+    h0 = m.hidden(3, x, cond, 0).cpu().numpy()
+    h1 = m.hidden(3, x, cond, 1).cpu().numpy()
+    v = m.velocity(3, x, cond)[0].cpu().numpy()
+    m.close()
+    obs = spec.Nv + spec.Na
+    lim = float(np.finfo(np.float32).max)
+    ln, rms = OD.layer_norm, OD.rms_norm
+    over = lambda s: s.sum(-1, keepdims=True) > lim  # noqa: E731
+    monkeypatch.setattr(OD, "layer_norm", lambda a, e: np.where(over((a - a.mean(-1, keepdims=True)) ** 2), 0, ln(a, e)))
+    monkeypatch.setattr(OD, "rms_norm", lambda a, e: np.where(over(a * a), 0, rms(a, e)))
+    c = OD.cond_vector(W, sig[3])
+    ref = OD.dit_layer(W, spec, 0, h0, c)
+    assert np.min(np.max(np.abs(h0[:, :obs]), -1)) > 1e19
+    np.testing.assert_array_equal(h1[:, :obs], h0[:, :obs])
+    upd = (ref - h0)[:, obs:]
+    err = float(np.max(np.abs((h1 - h0)[:, obs:] - upd)) / np.max(np.abs(upd)))
+    vref = OD.final_layer(W, spec, h1, c)
+    verr = float(np.max(np.abs(v - vref)) / np.max(np.abs(vref)))
+    print(f"{dtype}: observation rows' update rel err {err:.2e}, velocity {verr:.2e}")
+    # float32: rounding of the stored h0 and h1 (two each) and the first-order
+    # bound of the sums (one 2^-24 per term); the velocity is a D-term sum
+    ulp = 2.0 ** -24 * float(np.max(np.abs(h1[:, obs:])) / np.max(np.abs(upd)))
+    tol = BF16_UPDATE_TOL if dtype == "bf16" else 4 * ulp + (spec.F + 3 * spec.D) * 2.0 ** -24
+    assert err <= tol and verr <= (2 * spec.D + 16) * 2.0 ** -24, (err, verr)
