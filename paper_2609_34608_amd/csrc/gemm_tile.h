@@ -147,7 +147,7 @@ __device__ __forceinline__ void store_tile(const GemmArgs& a, const f32x4 (&acc)
           ss += __shfl_xor(ss, 16, 64);
           ss += __shfl_xor(ss, 32, 64);
           const f32x4* gain = sec == 0 ? qg : kg;
-          const float rs = qo.qk_norm ? rsqrt_newton(ss * (1.0f / DH) + qo.eps) : 1.0f;
+          const float rs = qo.qk_norm ? row_scale<E>(ss * (1.0f / DH) + qo.eps) : 1.0f;
           if (m < a.M) {
             E* dst = static_cast<E*>(sec == 0 ? qo.q : qo.k) + (((size_t)b * qo.H + head) * qo.Tpad + t) * DH;
 #pragma unroll

@@ -246,7 +246,7 @@ __global__ __launch_bounds__(256) void ln_modulate_kernel(const float* __restric
     const float t = (a * a + b * b) + (c * c + d * d);
     q += i < N4 - 1 || live ? t : 0.f;
   }
-  const float rstd = rsqrt_newton(wave_sum(q) / (float)D + eps);
+  const float rstd = row_scale<TOut>(wave_sum(q) / (float)D + eps);
   TOut* ur = u + (size_t)row * D;
 #pragma unroll
   for (int i = 0; i < N4; ++i) {
