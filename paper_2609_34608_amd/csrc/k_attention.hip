@@ -921,7 +921,6 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(AttnArgs a) {
 
 }  // namespace
 
-// grid for qt query tiles per wave and nw waves per block
 // (qt, nw, st): query tiles of 16 per wave, waves per block, LDS stages of
 // one 64-key K / V^T tile.  Only the instantiated combinations are accepted.
 hipError_t launch_attention_cfg(const AttnArgs& a, int qt, int nw, int st, hipStream_t s, int form) {
@@ -988,55 +987,19 @@ float attention_score_bound(const float* q_g, const float* k_g) {
 template <int DH>
 hipError_t launch_attention_f32(const AttnArgs& a, hipStream_t s) {
   const int tiles = (a.T + 15) / 16, heads = a.B * a.H;
-  const long units = (long)tiles * heads;
-  if (units >= 8192) launch_k(attn_f32_kernel<DH, 2, 1>, dim3((tiles + 7) / 8, heads), 256, 0, s, a);
-  else if (units >= 2048) launch_k(attn_f32_kernel<DH, 1, 1>, dim3((tiles + 3) / 4, heads), 256, 0, s, a);
-  else launch_k(attn_f32_kernel<DH, 1, 4>, dim3(tiles, heads), 256, 0, s, a);
+  switch (plan_attention_f32(a.T, heads)) {
+    case ATTN_F32_TWO_TILES: launch_k(attn_f32_kernel<DH, 2, 1>, dim3((tiles + 7) / 8, heads), 256, 0, s, a); break;
+    case ATTN_F32_ONE_TILE: launch_k(attn_f32_kernel<DH, 1, 1>, dim3((tiles + 3) / 4, heads), 256, 0, s, a); break;
+    default: launch_k(attn_f32_kernel<DH, 1, 4>, dim3(tiles, heads), 256, 0, s, a); break;
+  }
   return hipGetLastError();
 }
 
-// Forms that the automatic choice picks from, and what a block costs: a CU
-// that holds c of its blocks at once (c <= occ, set by their registers) takes
-// about ceil(T / 64) * per[c-1] + fix[c-1] us, least-squares fits to timings
-// of every form at 52 sizes (B 1 to 16, 4 to 32 heads, T 64 to 12000; standard
-// deviation 4-10%).  More queries per wave share each K / V^T read but leave
-// larger remainders in the last round; short sequences of few heads split the
-// keys over two groups of four waves (T = 864, 12 heads: 8.4 us against 8.9).
-struct AttnCfg {
-  AttnForm form;
-  int qt, nw, occ;
-  float per[5], fix[5];
-};
-constexpr AttnCfg kBounded[] = {
-    {ATTN_PLAIN, 4, 8, 1, {1.53f}, {5.0f}},
-    {ATTN_PLAIN, 3, 4, 2, {0.84f, 1.19f}, {3.8f, 5.8f}},
-    {ATTN_PLAIN, 2, 4, 3, {0.62f, 0.87f, 1.24f}, {3.6f, 5.2f, 5.8f}},
-    {ATTN_PLAIN, 1, 4, 5, {0.41f, 0.60f, 0.78f, 1.07f, 1.29f}, {3.2f, 3.8f, 4.7f, 4.9f, 3.4f}},
-    {ATTN_PLAIN_KSPLIT, 1, 4, 2, {0.31f, 0.51f}, {3.9f, 3.8f}},
-};
-constexpr AttnCfg kRunning[] = {
-    {ATTN_RUNNING, 3, 8, 1, {1.37f}, {3.9f}},
-    {ATTN_RUNNING, 3, 4, 2, {0.86f, 1.32f}, {4.4f, 6.9f}},
-    {ATTN_RUNNING, 2, 4, 2, {0.61f, 0.94f}, {4.1f, 5.7f}},
-    {ATTN_RUNNING, 1, 4, 4, {0.50f, 0.64f, 0.89f, 1.05f}, {3.3f, 4.2f, 4.7f, 4.8f}},
-};
-
-// The form of the smallest cost: over those sizes 1.7% (bounded) and 1.0%
-// (running max) slower than the fastest form on average, where the fixed
-// rules before were 5% and 10%.
+// the form of the smallest cost
 template <int N>
 hipError_t launch_cheapest(const AttnArgs& a, const AttnCfg (&cfgs)[N], hipStream_t s) {
-  const AttnCfg* best = nullptr;
-  double bc = 0.0;
-  for (const AttnCfg& c : cfgs) {
-    const int qb = c.qt * c.nw * 16;
-    const long blocks = (long)((a.T + qb - 1) / qb) * a.B * a.H, n = (blocks + 255) / 256;
-    const int rem = (int)(n % c.occ), tiles = a.Tpad / kKB;
-    double v = (double)(n / c.occ) * (tiles * c.per[c.occ - 1] + c.fix[c.occ - 1]);
-    if (rem) v += tiles * c.per[rem - 1] + c.fix[rem - 1];
-    if (!best || v < bc) best = &c, bc = v;
-  }
-  return launch_attention_cfg(a, best->qt, best->nw, 2, s, best->form);
+  const AttnCfg& c = cfgs[plan_attention(cfgs, a.T, a.B * a.H)];
+  return launch_attention_cfg(a, c.qt, c.nw, 2, s, c.form);
 }
 
 hipError_t launch_attention(const AttnArgs& a, bool bf16_mode, hipStream_t s) {
@@ -1053,9 +1016,6 @@ hipError_t launch_attention(const AttnArgs& a, bool bf16_mode, hipStream_t s) {
     return launch_attention_cfg(a, 1, 4, 2, s, ATTN_PLAIN_KSPLIT);
   }
   if (bf16_mode) return launch_cheapest(a, kRunning, s);
-  // fp32: enough 16-query tiles for two waves per SIMD without a key split
-  // (2048 waves), else four waves split the keys of one tile; two tiles per
-  // wave (half the K / V^T traffic) once that still leaves four waves per SIMD
   if (a.T <= 0 || a.Tpad % kKB || a.T > a.Tpad || a.T <= a.Tpad - kKB) return hipErrorInvalidValue;
   if (a.dh == 64) return launch_attention_f32<64>(a, s);
   if (a.dh == 32) return launch_attention_f32<32>(a, s);

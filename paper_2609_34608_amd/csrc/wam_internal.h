@@ -7,6 +7,7 @@
 
 #include <utility>
 
+#include "plan.h"
 #include "wam.h"
 
 namespace wam {
@@ -180,12 +181,9 @@ struct AttnArgs {
   int variant;  // WAM_ATTN_*: AUTO picks by shape; bounded forms need bounded set
 };
 hipError_t launch_attention(const AttnArgs& a, bool bf16_mode, hipStream_t s);
-// bf16 kernel forms: running max; and with a.bounded, the fixed reference in
-// a software-pipelined loop, a plain loop (also with two wave groups that
-// split the keys: 2 nw waves), or the ping-pong form (8 waves in two groups,
-// nw ignored)
-enum AttnForm : int { ATTN_RUNNING = 0, ATTN_PIPELINED = 1, ATTN_PLAIN = 2, ATTN_PINGPONG = 3, ATTN_PLAIN_KSPLIT = 4 };
-// qt query tiles of 16 per wave, nw waves per block, st K / V^T stages
+// qt query tiles of 16 per wave, nw waves per block (ping-pong: 8 in two
+// groups, nw ignored), st K / V^T stages; every form but ATTN_RUNNING needs
+// a.bounded
 hipError_t launch_attention_cfg(const AttnArgs& a, int qt, int nw, int st, hipStream_t s, int form = ATTN_RUNNING);
 // Largest score magnitude, log2 units, that the bf16 QKV epilogue can produce
 // for head size 64 with QK-norm gains q_g, k_g (host arrays of 64)

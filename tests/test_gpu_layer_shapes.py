@@ -70,14 +70,22 @@ def test_bf16_layer(dev, B, T, D, F):
     assert err <= BF16_UPDATE_TOL, err
 
 
-# bf16 attention forms of the automatic choice, bounded (QK-norm) and running
-# max (without): (B, T, D).  Short sequences of few heads (key split, 16 queries
-# per wave) to grids of several blocks per CU (32, 48 and 64 queries per wave),
-# lengths off every block of queries; the scores of the unnormalised model
-# spread over tens of log2 units, so the running max moves.
+# Attention forms of the automatic choice, bounded (QK-norm) and running max
+# (without): (B, T, D).  Short sequences of few heads (key split, 16 queries per
+# wave; one key tile, so that the second key group gets none) to grids of several
+# blocks per CU (32, 48 and 64 queries per wave, 48 over eight waves), lengths off
+# every block of queries and short enough in the last block that whole waves lie
+# past T; every form of both tables is among them
+# (tests/test_plan_coverage.py).  The scores of the unnormalised model spread over
+# tens of log2 units, so the running max moves.
+BF16_ATTENTION = [
+    (1, 37, 64), (1, 449, 320), (4, 333, 1024), (16, 150, 512), (1, 2211, 512), (2, 1130, 1088),
+    (16, 40, 1088), (1, 450, 64), (16, 513, 128), (16, 646, 192), (16, 769, 448), (16, 782, 320), (8, 1544, 256),
+]
+
+
 @pytest.mark.parametrize("qk_norm", [True, False])
-@pytest.mark.parametrize("B,T,D", [(1, 37, 64), (1, 449, 320), (4, 333, 1024), (16, 150, 512), (1, 2211, 512),
-                                   (2, 1130, 1088)])
+@pytest.mark.parametrize("B,T,D", BF16_ATTENTION)
 def test_bf16_attention_forms(dev, B, T, D, qk_norm):
     err, _ = _update_error(dev, _spec("bf16", B, T, D, 64, 2 * D, qk_norm), weight_std=0.02 if qk_norm else 0.045)
     print(f"bf16 attention B={B} T={T} D={D} qk_norm={qk_norm}: update rel err {err:.2e}")
