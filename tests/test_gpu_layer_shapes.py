@@ -39,15 +39,25 @@ def _spec(dtype, B, T, D, dh, F, qk_norm=True):
                                         qk_norm=qk_norm)
 
 
-# float32: (B, T, D, head size, F).  Lengths around the 16-query tiles and the
+# (B, T, D, head size, F, QK-norm).  Lengths around the 16-query tiles and the
 # 64-key tiles (one to five key tiles over four waves, so some waves get none);
-# 2112 query tiles (no key split) and 8320 (two tiles per wave); projections in
-# 32x32 / 32x64 and 64x64 tiles; head sizes 32 and 64, QK-norm on and off.
-@pytest.mark.parametrize("B,T,D,dh,F,qk_norm", [
+# head sizes 32 and 64; each of the three attention forms at both (2112 and more
+# query tiles: no key split; 8320 and more: two tiles per wave) and each
+# projection tile in each epilogue that the planner gives it, with rows and
+# columns left over.  tests/test_plan_coverage.py checks that none is missing.
+FP32_LAYERS = [
     (1, 3, 64, 32, 64, True), (1, 16, 64, 64, 192, True), (2, 17, 128, 32, 320, False), (1, 63, 192, 64, 768, True),
     (3, 64, 128, 64, 512, True), (1, 65, 320, 32, 1280, True), (1, 129, 192, 32, 448, False),
     (2, 321, 256, 64, 1024, True), (1, 2100, 512, 32, 512, True), (16, 1030, 256, 32, 256, True),
-])
+    (8, 43, 64, 64, 2240, True), (16, 34, 64, 64, 3008, False), (16, 74, 64, 64, 2752, True),
+    (16, 119, 192, 64, 128, True), (16, 125, 192, 32, 512, True), (8, 139, 704, 32, 128, False),
+    (16, 139, 320, 64, 128, True), (16, 268, 576, 64, 576, True), (16, 210, 320, 32, 320, True),
+    (16, 319, 320, 64, 192, False), (16, 474, 448, 32, 128, True), (16, 709, 768, 64, 128, True),
+    (1, 864, 768, 64, 3072, True),
+]
+
+
+@pytest.mark.parametrize("B,T,D,dh,F,qk_norm", FP32_LAYERS)
 def test_float32_layer(dev, B, T, D, dh, F, qk_norm):
     err, ulp = _update_error(dev, _spec("fp32", B, T, D, dh, F, qk_norm))
     print(f"fp32 B={B} T={T} D={D} dh={dh} F={F}: update rel err {err:.2e}, h rounding {ulp:.2e}")

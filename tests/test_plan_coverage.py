@@ -42,6 +42,25 @@ def _table(ask, name):
     return set(ask([f"table {name}"])[0])
 
 
+def _projections(ask, dtype, sizes, remainders):
+    """{(tile, epilogue)} of the four projections of (B, T, D, dh, F) sizes; with
+    remainders, only those whose last row tile is not full and, of 256 columns,
+    whose last column tile is not full."""
+    lines = []
+    for B, T, D, dh, F in sizes:
+        lines += [f"{dtype} {B * T} {n} {k} {int(qkv)}" for n, k, qkv in
+                  ((3 * D, D, True), (D, D, False), (F, D, False), (D, F, False))]
+    found = set()
+    for i, tile in enumerate(ask(lines)):
+        B, T, D, dh, F = sizes[i // 4]
+        N, epi = ((3 * D, f"qkv{dh}"), (D, "gated"), (F, "gelu"), (D, "gated"))[i % 4]
+        bm, bn, _ = map(int, tile[0].split("x"))
+        if remainders and (B * T % bm == 0 or (bn == 256 and N % bn == 0)):
+            continue
+        found.add((tile[0], epi))
+    return found
+
+
 def _sweep(n, fp32):
     rng = random.Random(17)
     out = []
@@ -52,6 +71,13 @@ def _sweep(n, fp32):
         if B * T <= 16000:
             out.append((B, T, D, rng.choice([32, 64]) if fp32 else 64, F))
     return out
+
+
+def test_float32_projection_tiles(ask):
+    chosen = _projections(ask, "fp32", _sweep(20000, True), False)
+    assert {t for t, _ in chosen} == _table(ask, "fp32")
+    missing = chosen - _projections(ask, "fp32", [s[:5] for s in shapes.FP32_LAYERS], True)
+    assert not missing, missing
 
 
 @pytest.mark.parametrize("kind", ["bounded", "running"])
@@ -75,3 +101,10 @@ def test_key_split_of_one_key_tile(ask):
     split = max(_table(ask, "bounded"))  # form 4: two wave groups split the keys
     assert split.startswith("4:")
     assert [split] in ask([f"bounded {T} {B * D // 64}" for B, T, D in sizes])
+
+
+def test_float32_attention_forms(ask):
+    sizes = [s[:4] for s in shapes.FP32_LAYERS if s[1] % 16]
+    got = {(f[0], dh) for (B, T, D, dh), f in
+           zip(sizes, ask([f"attn_fp32 {T} {B * D // dh}" for B, T, D, dh in sizes]))}
+    assert got == {(f, dh) for f in "012" for dh in (32, 64)}
