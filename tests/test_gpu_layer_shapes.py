@@ -16,9 +16,10 @@ def dev():
     return device()
 
 
-def _update_error(dev, spec, k=3, weight_std=0.05):
+def _update_error(dev, spec, k=3, weight_std=0.05, rows=None):
     """max |update error| over max |update|, and the float32 spacing of h over
-    max |update| (the rounding of the stored h)."""
+    max |update| (the rounding of the stored h); over the given rows of B T, or
+    all."""
     from paper_2609_34608_amd import runtime as R
     W = make_weights(spec, bias_std=0.02, gain_std=0.1, weight_std=weight_std)
     m = R.WamModel(R.config_of(spec), W, device=dev)
@@ -28,7 +29,13 @@ def _update_error(dev, spec, k=3, weight_std=0.05):
     h0 = m.hidden(k, x, cond, 0).cpu().numpy()
     h1 = m.hidden(k, x, cond, 1).cpu().numpy()
     m.close()
-    ref = OD.dit_layer(W, spec, 0, h0, OD.cond_vector(W, sig[k])) - h0
+    c = OD.cond_vector(W, sig[k])
+    if rows is None:
+        ref = OD.dit_layer(W, spec, 0, h0, c) - h0
+    else:
+        ref = OD.dit_layer_rows(W, spec, 0, h0, c, rows)
+        h0, h1 = (h.reshape(-1, spec.D)[rows] for h in (h0, h1))
+        ref -= h0
     upd = np.max(np.abs(ref))
     return float(np.max(np.abs((h1 - h0) - ref)) / upd), float(2.0 ** -24 * np.max(np.abs(h1)) / upd)
 
@@ -66,17 +73,42 @@ def test_float32_layer(dev, B, T, D, dh, F, qk_norm):
     assert err <= 4 * ulp + (F + 3 * D) * 2.0 ** -24, (err, ulp)
 
 
-# bf16: (B, T, D, F).  Row counts off every tile height, widths 3 D, D and F
-# that end inside a 256-, 128- or 64-column tile (odd head counts among them),
-# from one block of rows to several rounds of the chip, so that small, two-per-
-# CU and 256-column tiles all run.
-@pytest.mark.parametrize("B,T,D,F", [
+# (B, T, D, F).  Row counts off every tile height, widths 3 D, D and F that end
+# inside a 128- or 64-column tile (odd head counts among them), from one block of
+# rows to several rounds of the chip.
+BF16_LAYERS = [
     (1, 3, 64, 128), (1, 70, 192, 512), (2, 137, 320, 1280), (1, 505, 640, 2560), (3, 400, 448, 1152),
     (2, 1100, 832, 2176), (2, 901, 1216, 4864), (4, 577, 1088, 2944), (1, 2650, 1600, 3200),
-])
+]
+
+
+@pytest.mark.parametrize("B,T,D,F", BF16_LAYERS)
 def test_bf16_layer(dev, B, T, D, F):
     err, _ = _update_error(dev, _spec("bf16", B, T, D, 64, F), weight_std=0.02)
     print(f"bf16 B={B} T={T} D={D} F={F}: update rel err {err:.2e}")
+    assert err <= BF16_UPDATE_TOL, err
+
+
+# (B, T, D, F).  With the sizes above, each projection tile in each epilogue that
+# the planner gives it (tests/test_plan_coverage.py), rows left over in every one
+# and columns too in the 256-column tiles: the last wave columns then lie past N
+# and leave before the epilogue.
+BF16_TILES = [
+    (2, 5513, 128, 512), (2, 4946, 320, 896), (1, 3, 256, 640), (2, 3126, 64, 256), (1, 2691, 192, 768),
+    (1, 5391, 192, 768), (2, 5514, 448, 1152), (3, 542, 640, 1664), (4, 605, 640, 2560), (2, 5541, 704, 1408),
+    (3, 3279, 1088, 2944), (2, 5426, 1344, 3584),
+]
+
+
+@pytest.mark.parametrize("B,T,D,F", BF16_TILES)
+def test_bf16_tiles(dev, B, T, D, F):
+    """Every column of sampled rows: the ends of the samples, the last row tile
+    (up to 320 rows), and rows of the others."""
+    M = B * T
+    rows = np.unique(np.r_[0, T - 1, M - 1 - T % 7, range(max(0, M - 320), M, 9), M - 1,
+                           np.random.default_rng(5).integers(0, M, 40)])
+    err, _ = _update_error(dev, _spec("bf16", B, T, D, 64, F), weight_std=0.02, rows=rows)
+    print(f"bf16 B={B} T={T} D={D} F={F}: {len(rows)} rows' update rel err {err:.2e}")
     assert err <= BF16_UPDATE_TOL, err
 
 

@@ -73,6 +73,15 @@ def _sweep(n, fp32):
     return out
 
 
+def test_bf16_projection_tiles(ask):
+    tested = [(B, T, D, 64, F) for B, T, D, F in shapes.BF16_LAYERS + shapes.BF16_TILES]
+    tested += [(B, T, D, 64, 2 * D) for B, T, D in shapes.BF16_ATTENTION]
+    chosen = _projections(ask, "bf16", _sweep(20000, False), False)
+    assert {t for t, _ in chosen} == _table(ask, "bf16")
+    missing = chosen - _projections(ask, "bf16", tested, True)
+    assert not missing, missing
+
+
 def test_float32_projection_tiles(ask):
     chosen = _projections(ask, "fp32", _sweep(20000, True), False)
     assert {t for t, _ in chosen} == _table(ask, "fp32")
