@@ -60,11 +60,7 @@ def kernel_class(name: str):
     m = re.search(r"gemm_bf16_kernel<\s*\d+,\s*\d+,\s*\d+,\s*\d+,\s*\d+,\s*\d+,\s*\d+,\s*(\d+)\s*[,>]", name)
     if m:
         return CLASS_NAMES[int(m.group(1))]
-    m = re.search(r"gemm_splitk_reduce_kernel<\s*\d+,\s*(\d+)>", name)  # second pass of a split GEMM
-    if m:
-        return CLASS_NAMES[int(m.group(1))]
-    for key, cls in (("attn_bf16", "attention"), ("rr_row_sums_kernel", "rr_gate"),
-                     ("rr_finish_kernel", "rr_gate"), ("rr_gate_partials_kernel", "rr_gate"),
+    for key, cls in (("attn_bf16", "attention"), ("rr_gate_partials_kernel", "rr_gate"),
                      ("rr_gate_finish_kernel", "rr_gate"), ("rr_inject_kernel", "rr_inject"),
                      ("rr_refresh_kernel", "rr_refresh")):
         if key in name:

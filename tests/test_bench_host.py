@@ -4,6 +4,7 @@ rocprofv3 kernel names to the timed classes, and the HBM traffic summary
 copy of known size) with its source-hash check."""
 import json
 import os
+import shutil
 import subprocess
 import sys
 
@@ -30,22 +31,36 @@ def test_more_than_one_gpu_is_refused(extra):
 
 
 @pytest.mark.parametrize("name,cls", [
-    ("void wam::gemm::gemm_bf16_kernel<256, 256, 2, 4, 2, 64, 3, 0, false>(wam::GemmArgs)", "gemm_qkv"),
-    ("void wam::gemm::gemm_bf16_kernel<256, 256, 2, 4, 2, 64, 2, 1, false>(wam::GemmArgs)", "gemm_proj"),
-    ("void wam::gemm::gemm_bf16_kernel<320, 256, 2, 4, 2, 64, 1, 2, false>(wam::GemmArgs)", "gemm_fc1"),
-    ("void wam::gemm::gemm_bf16_kernel<64, 64, 2, 2, 4, 64, 2, 3, true>(wam::GemmArgs)", "gemm_fc2"),
-    ("void wam::gemm::gemm_splitk_reduce_kernel<2, 3>(wam::GemmArgs, int)", "gemm_fc2"),
+    ("void wam::gemm::gemm_bf16_kernel<256, 256, 2, 4, 2, 64, 3, 0>(wam::GemmArgs)", "gemm_qkv"),
+    ("void wam::gemm::gemm_bf16_kernel<256, 256, 2, 4, 2, 64, 2, 1>(wam::GemmArgs)", "gemm_proj"),
+    ("void wam::gemm::gemm_bf16_kernel<320, 256, 2, 4, 2, 64, 1, 2>(wam::GemmArgs)", "gemm_fc1"),
+    ("void wam::gemm::gemm_bf16_kernel<64, 64, 2, 2, 4, 64, 2, 3>(wam::GemmArgs)", "gemm_fc2"),
     ("void wam::(anonymous namespace)::attn_bf16_kernel<4, 8, 2, true, 1>(wam::AttnArgs)", "attention"),
     ("void wam::(anonymous namespace)::rr_gate_partials_kernel<8>(wam::RRGateArgs)", "rr_gate"),
     ("wam::(anonymous namespace)::rr_gate_finish_kernel(wam::RRGateArgs)", "rr_gate"),
     ("wam::(anonymous namespace)::rr_inject_kernel(float*, float const*, double const*, int)", "rr_inject"),
     ("wam::(anonymous namespace)::rr_refresh_kernel(float const*, float const*, float*, long, int const*)",
      "rr_refresh"),
-    ("void wam::(anonymous namespace)::final_kernel<4, 4, 6, 8>(wam::FinalArgs)", None),
+    ("void wam::(anonymous namespace)::final_kernel<24>(wam::FinalArgs)", None),
     ("__amd_rocclr_copyBuffer", None),
 ])
 def test_kernel_class(name, cls):
     assert bench.kernel_class(name) == cls
+
+
+def test_kernel_class_of_the_built_kernels():
+    """Every bf16 projection and attention kernel of the library has a class by
+    its name, and every class has a kernel."""
+    lib = os.path.join(ROOT, "paper_2609_34608_amd", "lib", "libwam.so")
+    nm = shutil.which("nm")
+    if not os.path.exists(lib) or not nm:
+        pytest.skip("library not built")
+    names = subprocess.run([nm, "-C", lib], capture_output=True, text=True, check=True, timeout=60).stdout.splitlines()
+    names = [n.split(" ", 2)[-1] for n in names if "_kernel" in n and "__device_stub__" not in n]
+    found = {n: bench.kernel_class(n) for n in names}
+    timed = {n: c for n, c in found.items() if "gemm_bf16_kernel<" in n or "attn_bf16" in n}
+    assert timed and all(timed.values()), [n for n, c in timed.items() if not c]
+    assert set(bench.CLASS_NAMES) <= set(found.values())
 
 
 _FIELDS = ["Dispatch_Id", "Kernel_Name", "Counter_Name", "Counter_Value", "Start_Timestamp", "End_Timestamp"]
