@@ -37,7 +37,6 @@
 namespace wam {
 namespace gemm {
 
-constexpr int kBK = 32;    // K per bf16 MFMA step (and its smallest stage depth)
 constexpr int kGroupM = 8;
 constexpr int kXcd = 8;
 
