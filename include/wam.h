@@ -325,7 +325,7 @@ int wam_adapt_state(wam_t h, int op, const void *args);
  * differences are summed on the device in runs (float64, fixed order) and the
  * run sums on the host.  Only this device form exists: the components are the
  * condition tensors, which already live on the device.  Uses the handle's
- * stream and workspace; synchronises. */
+ * stream and its pinned host buffer; synchronises. */
 int wam_consistency_score(wam_t h, int n_components, const float *const *u_hat,
                           const float *const *u, const int64_t *n, const double *delta,
                           const double *weight, double *S_out);

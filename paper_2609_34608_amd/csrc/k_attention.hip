@@ -7,12 +7,12 @@
 // bf16 flash attention (dh = 64): each wave owns 16*QT queries and keeps their
 // Q fragments in registers.  Scores are formed transposed, S^T = K Q^T, with
 // v_mfma_f32_16x16x32_bf16 so that a lane's accumulators all belong to one
-// query column: the online-softmax rescale of O^T = V^T P^T is lane-local and
-// the running max needs only two cross-lane steps.  P^T feeds the second MFMA
-// straight from registers; the key order inside the 32-key contraction is the
-// one the score accumulators hold, and the QKV epilogue stores V^T with its
-// keys permuted to match (vt_key_pos), so each V^T operand is one 16-byte LDS
-// read.  K and V^T tiles of 64 keys (128-byte rows, 16-byte chunks XOR-swizzled
+// query column: the online-softmax rescale of O^T = V^T P^T is lane-local, and
+// so is the test whether a tile moves the running max (only a tile that does
+// takes two cross-lane steps).  P^T feeds the second MFMA straight from
+// registers; the key order inside the 32-key contraction is the one the score
+// accumulators hold, and the QKV epilogue stores V^T with its keys permuted to
+// match (vt_key_pos), so each V^T operand is one 16-byte LDS read.  K and V^T tiles of 64 keys (128-byte rows, 16-byte chunks XOR-swizzled
 // by row & 7: conflict-free ds_read_b128) go through ST LDS stages filled by
 // global_load_lds_dwordx4, ST-1 in flight.  Softmax runs in fp32 with exp2: q
 // arrives pre-scaled by log2(e)/sqrt(dh) (QKV epilogue), and the score

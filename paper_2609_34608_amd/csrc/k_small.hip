@@ -208,8 +208,9 @@ __global__ __launch_bounds__(512) void embed_v4_kernel(EmbedArgs a) {
 // ahead of the reductions (with a run-time count the compiler emitted one load
 // and one wait per chunk).  RAG: D is not a multiple of 256 (it is one of 64),
 // and the lanes of the last chunk past D load the row's start again and count
-// as zero.  HBM bound (6 bytes an element); D = 1216, 5754 rows: 17.5 us
-// with one element per lane and load, 8.8 us here.
+// as zero.  HBM bound (6 bytes an element with bf16 results, 8 with float32);
+// D = 1216, 5754 rows, bf16: 17.5 us with one element per lane and load, 8.8 us
+// here.
 template <int N4, bool RAG, typename TOut>
 __global__ __launch_bounds__(256) void ln_modulate_kernel(const float* __restrict__ h, const float* __restrict__ shift,
                                                           const float* __restrict__ scale, TOut* __restrict__ u,
@@ -653,7 +654,7 @@ __device__ __forceinline__ double run_sq_sum(const float* p, const float* q, dou
 // coefficient sigma_b0 / (sigma_r rms) (0 for a zero direction).  Up to 2048
 // blocks of the remap itself (one round of the chip) every one of them does
 // that for the branches it touches while its loads are in flight, two launches
-// in all: 4 x 154 K elements 12.4 -> 9.5 us.  Beyond, repeating the sum in
+// in all: 4 x 154 K elements 12.4 -> 9.7 us.  Beyond, repeating the sum in
 // every block costs more than the launch it saves (16 M elements: 55 us against
 // 52) and one block per (sample, branch) does it in between.
 template <bool VEC>
@@ -701,11 +702,12 @@ __global__ __launch_bounds__(256) void remap_finish_kernel(RemapArgs a) {
 // x[j] = x_bar[j+shift] + sigma_b0 d[j+shift] on mapped slots, sigma_b0 eps[j]
 // elsewhere.  Slot j of a branch of width w is mapped when j + shift < slots,
 // i.e. when the element index within the branch plus shift * w stays inside
-// the branch.  Grid (runs of 256 thread items, sample): with VEC an item is four consecutive elements with 16-byte loads and stores (the host has
-// checked that the pointers, both branch lengths and both shifted offsets are
-// multiples of four floats, so a group lies in one branch and is mapped or
-// unmapped as a whole); otherwise one element.  Every element is computed by
-// the same expression either way.
+// the branch.  Grid (runs of 256 thread items, sample): with VEC an item is
+// four consecutive elements with 16-byte loads and stores (the host has checked
+// that the pointers, both branch lengths and both shifted offsets are multiples
+// of four floats, so a group lies in one branch and is mapped or unmapped as a
+// whole); otherwise one element.  Every element is computed by the same
+// expression either way.
 __device__ __forceinline__ float remap_value(float xb, float xr, double coef) {
   const double x = (double)xb;
   return (float)(x + ((double)xr - x) * coef);

@@ -5,17 +5,17 @@
 
 namespace wam {
 
-// ---------------------------------------------------------------- configs
-// Tile shapes and what a tile costs.  A CU that holds c
-// blocks at once (c <= occ) finishes them in about K / 64 * per[c-1] +
-// fix[c-1] us; the constants are least-squares fits to timings of every
-// configuration at the four projections of 57 model sizes (64 to 12000 rows,
-// D 256 to 2048), standard deviation 7-12%.  What they show: 256-column tiles
-// over 8 waves do the most work per byte loaded and win where their blocks
-// fill whole rounds of the 256 CUs; 128-column tiles over 4 waves leave room
-// for two blocks per CU, whose barriers and epilogues overlap, and waste less
-// in the last round; small tiles spread short sequences over the chip, where
-// a launch costs ~3 us whatever it does.
+// ---------------------------------------------------------------- projections
+// bf16 tile shapes and what a tile costs.  A CU that holds c blocks at once
+// (c <= occ) finishes them in about K / 64 * per[c-1] + fix[c-1] us; the
+// constants are least-squares fits to timings of every configuration at the
+// four projections of 57 model sizes (64 to 12000 rows, D 256 to 2048),
+// standard deviation 7-12%.  What they show: 256-column tiles over 8 waves do
+// the most work per byte loaded and win where their blocks fill whole rounds of
+// the 256 CUs; 128-column tiles over 4 waves leave room for two blocks per CU,
+// whose barriers and epilogues overlap, and waste less in the last round; small
+// tiles spread short sequences over the chip, where a launch costs ~3 us
+// whatever it does.
 struct TileCfg {
   int bm, bn, wgm, wgn, st, bk;  // rows x columns, waves (rows x columns), LDS stages, K per stage
   int occ;
@@ -36,6 +36,7 @@ constexpr TileCfg kCfgs[] = {
     {32, 64, 2, 1, 4, 64, 3, {0.20f, 0.26f, 0.38f}, {3.18f, 3.62f, 2.20f}},
     {32, 32, 2, 2, 4, 128, 2, {0.10f, 0.16f}, {2.90f, 3.00f}},
 };
+
 // float32 operands: the fp32 matrix rate (157 TFLOP/s, a sixteenth of bf16)
 // leaves loads and LDS far from their limits at any tile, so the tile has to
 // spread the work evenly; large ones run their MFMAs with fewer gaps (96x128
@@ -52,6 +53,7 @@ constexpr TileCfg kF32Cfgs[] = {
     {32, 32, 2, 2, 4, 32, 3, {0.42f, 0.65f, 0.92f}, {2.5f, 2.9f, 1.6f}},
     {16, 64, 1, 1, 4, 32, 4, {1.10f, 1.14f, 1.21f, 1.27f}, {3.1f, 3.4f, 3.6f, 2.5f}},
 };
+
 inline double tile_cost(const TileCfg& t, int M, int N, int K) {
   const long blocks = (long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
   const long n = (blocks + 255) / 256;  // blocks of the busiest CU

@@ -177,8 +177,8 @@ def test_bf16_degenerate_shapes_match_oracle(dev, shape):
 @pytest.mark.parametrize("D,H", [(192, 3), (1088, 17)])
 def test_bf16_odd_head_counts_match_oracle(dev, D, H):
     """bf16 mode with an odd number of heads: the QKV output width 192 H is a
-    multiple of 64 but not of 128 (its own GEMM tile); D not a multiple of 256
-    takes the generic LayerNorm, and D = 1088 the row-wise final layer."""
+    multiple of 64 but not of 128, so a 128-column tile ends past it; D is not a
+    multiple of 256, so LayerNorm masks its last chunk."""
     from paper_2609_34608_amd import runtime as R
     spec = get_workload("small").replace(L=1, D=D, H=H, F=4 * D, Nv=40, Na=16, No=8, B=2)
     W = make_weights(spec, bias_std=0.02, gain_std=0.1)
