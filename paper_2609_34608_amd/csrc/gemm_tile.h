@@ -15,18 +15,18 @@
 // does not matter as long as both operands share it), so the stages, the
 // swizzle and the operand reads are the same bytes in both types.
 //
-// K advances BK elements (64 to 256 bytes) at a time through ST LDS stages.
+// K advances BK elements (128 or 256 bytes) at a time through ST LDS stages.
 // Each stage holds BM activation rows and BN weight rows, filled straight
 // from global memory by global_load_lds_dwordx4 (16 bytes per lane, one 1 KiB
 // run of LDS per instruction, no register staging): ST-1 stages are in flight
 // while one is multiplied.  Inside a row the 16-byte chunks are XOR-swizzled
-// ((row >> 1) & 3 for 64-byte rows, row & 7 for longer ones), which keeps the
-// ds_read_b128 operand reads (16 rows x one chunk per 16 lanes) free of bank
-// conflicts; the loads pick their global chunk so that the LDS image comes out
-// swizzled.  A deeper stage gives each wave BK/32 MFMA k-steps per barrier,
-// which is what short tiles (small M) need.  The compiler cannot follow
-// the LDS writes of these loads, so the loop waits on vmcnt itself and uses a
-// bare s_barrier (a workgroup fence would drain every load in flight).
+// (row & 7), which keeps the ds_read_b128 operand reads (16 rows x one chunk per
+// 16 lanes) free of bank conflicts; the loads pick their global chunk so that
+// the LDS image comes out swizzled.  The longer rows give each wave four MFMA
+// k-steps per barrier instead of two, which is what the smallest tiles need.
+// The compiler cannot follow the LDS writes of these loads, so the loop waits on
+// vmcnt itself and uses a bare s_barrier (a workgroup fence would drain every
+// load in flight).
 // Blocks are renumbered so that each XCD (dispatch is round-robin over 8 XCDs)
 // gets a contiguous run of a grouped tile order and shares A rows / W columns
 // in its own L2.
@@ -48,12 +48,8 @@ typedef __attribute__((address_space(1))) void global_void;
 // scalar-memory operation outstanding
 constexpr int waitcnt_vm_lgkm0(int n) { return (n & 0xf) | ((n >> 4) << 14) | (0x7 << 4); }
 
-// XOR swizzle of the 16-byte chunks of an LDS row of CPR chunks
-template <int CPR>
-__device__ __forceinline__ int chunk_swizzle(int row) {
-  if constexpr (CPR == 4) return (row >> 1) & 3;
-  else return row & 7;
-}
+// XOR swizzle of the 16-byte chunks of an LDS row (8 or 16 chunks)
+__device__ __forceinline__ int chunk_swizzle(int row) { return row & 7; }
 
 // Operand chunk (16 bytes) of one lane and the MFMA step that consumes a
 // weight and an activation chunk.
@@ -223,7 +219,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a) {
   constexpr int NI = ROWS / RPI;               // load instructions per stage
   constexpr int IPW = NI / NW;                 // ... per wave
   constexpr int KS = CPR / 4;                  // MFMA k-steps per stage (four chunks each)
-  static_assert(CPR == 4 || CPR == 8 || CPR == 16, "stage depth");
+  static_assert(CPR == 8 || CPR == 16, "stage depth");
   static_assert(TM >= 1 && TN >= 1, "wave tile too small");
   static_assert(IPW >= 1 && IPW * NW == NI, "stage rows / wave mismatch");
   static_assert(EPI != EPI_QKV || WN % DH == 0, "QKV epilogue needs whole heads per wave");
@@ -252,7 +248,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a) {
 #pragma unroll
   for (int j = 0; j < IPW; ++j) {
     const int row = RPI * (wid + NW * j) + lane / CPR;
-    const int col = ((lane % CPR) ^ chunk_swizzle<CPR>(row)) * EPC;
+    const int col = ((lane % CPR) ^ chunk_swizzle(row)) * EPC;
     src[j] = row < BM ? A + (size_t)min(m0 + row, a.M - 1) * K + col
                       : W + (size_t)min(n0 + row - BM, a.N - 1) * K + col;
   }
@@ -274,7 +270,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a) {
   // lr of each 16-row tile (tile row offsets are multiples of 16, so the
   // swizzle depends on lr only)
   const int lr = lane % 16, lg = lane / 16;
-  const int sw = chunk_swizzle<CPR>(lr);
+  const int sw = chunk_swizzle(lr);
   const int arow = (wm * WM + lr) * BK;
   const int wrow = (BM + wn * WN + lr) * BK;
   auto compute = [&](auto S) __attribute__((always_inline)) {
